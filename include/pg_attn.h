@@ -81,7 +81,7 @@ size_t pg_attn_fwd_workspace_size(int n_groups, int n_suffixes, int total_prefix
                                   int h_kv, int head_dim);
 
 /* Workspace bytes pg_attn_bwd needs for these sizes (host call, no GPU use; 0 for negative sizes). It holds
- * the tile plan, rowsum(dO*O) and, when the walks of long prefix key tiles are split over several workgroups,
+ * the tile plan, two float values per query row and head (rowsum(dO*O) and the log-sum-exp) and, when the walks of long prefix key tiles are split over several workgroups,
  * their fp32 dK/dV partial sums. */
 size_t pg_attn_bwd_workspace_size(int n_groups, int n_suffixes, int total_prefix, int total_suffix, int h_q,
                                   int h_kv, int head_dim);

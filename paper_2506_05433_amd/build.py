@@ -27,6 +27,9 @@ def command(out: str = OUT, extra=()) -> list:
     return [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-shared", "-fPIC",
             # packed fp32 VALU forms are kept out of the generated code on purpose
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+            # results of matrix products that vector instructions read next stay in VGPRs also in
+            # kernels that use AGPRs (pg_bwd_wide.hpp keeps its accumulators there)
+            "-mllvm", "-amdgpu-mfma-vgpr-form=1",
             "-o", out, SRC, *extra]
 
 

@@ -2,6 +2,7 @@
 // host-side argument checks, workspace layout, and the launch sequence.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -13,6 +14,7 @@
 
 #include "../../include/pg_attn.h"
 #include "pg_bwd.hpp"
+#include "pg_bwd_wide.hpp"
 #include "pg_fwd.hpp"
 #include "pg_plan.hpp"
 #include "pg_last.hpp"
@@ -46,9 +48,10 @@ long ceil_div_l(long a, long b) { return (a + b - 1) / b; }
 
 // Workspace layout shared by the forward and backward calls.
 struct Layout {
-  size_t hdr, ginfo, qoff, kvoff, qtiles, qorder, kvtiles, kvorder, seg, dsum, part, xrow, total;
+  size_t hdr, ginfo, qoff, kvoff, qtiles, qorder, kvtiles, kvorder, seg, dsum, lse2, part, xrow, total;
   long max_q, max_kv;
   int kv_chunks, split;
+  int bkv;  // keys per key tile: kKvBN, or kWideBN for dkdv_wide_kernel
 };
 
 // Pieces each prefix key tile's query walk is split into for the dK/dV kernel: enough
@@ -59,11 +62,15 @@ struct Layout {
 // least 16 64-row query tiles of the average walk (a group's rows, once per query head of
 // the kv head): shorter pieces cost more in their fixed start-up and in the reduce launch
 // than they save. A grid of at most 128 key tiles (half the CUs) runs as long as its
-// longest walk whatever the total work, so there pieces of one such tile pay off.
-int kv_chunks_for(int ng, int tp, int ts, int h_q, int h_kv) {
+// longest walk whatever the total work, so there pieces of one such tile pay off. With 256-key
+// tiles (one workgroup per CU) about 384 pieces are best, and two up to 768: one group of P 4096,
+// 32/8 heads (136 tiles) takes 913, 909, 1050, 982 us with 2, 3, 4, 6 pieces, P 16384 (520 tiles)
+// 6.30 ms with one and 6.17 with two.
+int kv_chunks_for(int ng, int tp, int ts, int h_q, int h_kv, int bkv) {
   if (tp <= 0 || h_kv <= 0) return 1;
-  const long tiles = (ceil_div_l(tp, pg::kKvBN) + ng) * (long)h_kv;
+  const long tiles = (ceil_div_l(tp, bkv) + ng) * (long)h_kv;
   long c = ceil_div_l(512, tiles);
+  if (bkv == pg::kWideBN) c = tiles >= 768 ? 1 : std::max(2L, ceil_div_l(384, tiles));
   const long walk = ceil_div_l((long)tp + ts, (long)(ng > 0 ? ng : 1) * 64) * (h_q / h_kv);
   const long min_piece = 2 * tiles <= 256 ? 1 : 16;
   if (c > walk / min_piece) c = walk / min_piece;
@@ -75,13 +82,25 @@ int kv_chunks_for(int ng, int tp, int ts, int h_q, int h_kv) {
 // tile walk, not the total work.
 constexpr long kSplitBelow = 256;
 
-Layout make_layout(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d, bool bwd) {
+// Whether the backward runs dkdv_wide_kernel (256-key tiles). It does the same work in fewer, longer
+// workgroups, so it needs enough of it: at least 80 tile steps (32 query rows x 256 keys) per CU in the
+// prefix walks, and prefixes long enough that a tile's 256 keys are rarely ragged. Measured (dK/dV
+// plus reduction, dkdv_kernel -> wide): 24 steps per CU 112 -> 123 us, 55 steps 194 -> 203 us, 112 steps
+// 335 -> 297 us, 232 steps 718 -> 675 us; 184 steps but prefixes of 300 rows 540 -> 608 us.
+bool use_wide(int dtype, int ng, int tp, int ts, int h_q, int h_kv) {
+  if (dtype != PG_BF16 || ng <= 0 || h_kv <= 0 || tp / 1024 < ng) return false;
+  const double walk = (double)(h_q / h_kv) * (0.5 * tp + ts) / ((double)ng * pg::kWideBQ);
+  return walk * (double)ceil_div_l(tp, pg::kWideBN) * h_kv >= 80.0 * 256.0;
+}
+
+Layout make_layout(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d, bool bwd, bool wide = false) {
   Layout L{};
-  L.kv_chunks = bwd ? kv_chunks_for(ng, tp, ts, h_q, h_kv) : 1;
+  L.bkv = wide ? pg::kWideBN : pg::kKvBN;
+  L.kv_chunks = bwd ? kv_chunks_for(ng, tp, ts, h_q, h_kv, L.bkv) : 1;
   L.split = (ceil_div_l(tp, pg::kFwdBM) + ceil_div_l(ts, pg::kFwdBM) + ng) * (long)h_q < kSplitBelow ? 1 : 0;
   // bounds of the tile lists in either tiling (splitting adds at most one tile per member)
   L.max_q = ceil_div_l(tp, pg::kFwdBM) + ceil_div_l(ts, pg::kFwdBM) + 2L * ng + ns;
-  L.max_kv = bwd ? (ceil_div_l(tp, pg::kKvBN) + ng) * L.kv_chunks + ceil_div_l(ts, pg::kKvBN) + ng + ns : 0;
+  L.max_kv = bwd ? (ceil_div_l(tp, L.bkv) + ng) * L.kv_chunks + ceil_div_l(ts, L.bkv) + ng + ns : 0;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
   const size_t rows = (size_t)tp + (size_t)ts;  // sizes are non-negative ints: no overflow in 64 bits
@@ -95,6 +114,7 @@ Layout make_layout(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d, boo
   L.kvorder = take(sizeof(int) * (size_t)(L.max_kv > 0 ? L.max_kv : 1));
   L.seg = take(sizeof(int) * (size_t)(ts > 0 ? ts : 1));
   L.dsum = bwd ? take(sizeof(float) * (size_t)h_q * (rows > 0 ? rows : 1)) : off;
+  L.lse2 = bwd && wide ? take(sizeof(float) * (size_t)h_q * (rows > 0 ? rows : 1)) : off;
   L.part = (bwd && L.kv_chunks > 1) ? take(sizeof(float) * (size_t)L.kv_chunks * 2 * (size_t)tp * h_kv * d) : off;
   L.xrow = bwd ? take(sizeof(int) * (rows > 0 ? rows : 1)) : off;
   L.total = off;
@@ -253,7 +273,7 @@ int launch_plan(const Common& c, const Layout& L, char* ws, const int32_t* cu_p,
   if (one_block) {
     // every tile list fits one block: groups, tiles and ranks in one launch
     hipLaunchKernelGGL(pg::plan_fused_kernel, dim3(1), dim3(pg::kPlanThreads), 0, st, cu_p, cu_s, gsz, c.ng, c.ns,
-                       c.tp, c.ts, pg::kFwdBM, pg::kKvBN, L.kv_chunks, L.split, L.max_q,
+                       c.tp, c.ts, pg::kFwdBM, L.bkv, L.kv_chunks, L.split, L.max_q,
                        bwd ? L.max_kv : 0x7fffffffL, hdr, gi, qoff, kvoff, qt, qo,
                        bwd ? (pg::TileDesc*)(ws + L.kvtiles) : nullptr, (int*)(ws + L.kvorder),
                        fused_seg ? (int*)(ws + L.seg) : nullptr);
@@ -279,13 +299,13 @@ void launch_plan_tiles(const Common& c, const Layout& L, char* ws, const int32_t
   int* qoff = (int*)(ws + L.qoff);
   int* kvoff = (int*)(ws + L.kvoff);
   hipLaunchKernelGGL(pg::plan_groups_kernel, dim3(1), dim3(pg::kPlanThreads), 0, st, cu_p, cu_s, gsz, c.ng, c.ns,
-                     c.tp, c.ts, pg::kFwdBM, pg::kKvBN, L.kv_chunks, L.split, L.max_q, bwd ? L.max_kv : 0x7fffffffL,
+                     c.tp, c.ts, pg::kFwdBM, L.bkv, L.kv_chunks, L.split, L.max_q, bwd ? L.max_kv : 0x7fffffffL,
                      hdr, gi, qoff, kvoff);
   auto* qt = (pg::TileDesc*)(ws + L.qtiles);
   int* qo = (int*)(ws + L.qorder);
   if (L.max_q > 0) {
     const int blocks = (int)ceil_div_l(L.max_q, 256);
-    hipLaunchKernelGGL(pg::plan_tiles_kernel, dim3(blocks), dim3(256), 0, st, cu_s, c.ng, pg::kFwdBM, pg::kKvBN,
+    hipLaunchKernelGGL(pg::plan_tiles_kernel, dim3(blocks), dim3(256), 0, st, cu_s, c.ng, pg::kFwdBM, L.bkv,
                        1, L.split, (int)L.max_q, hdr, gi, qoff, qt, 0);
     hipLaunchKernelGGL(pg::plan_rank_kernel, dim3(blocks), dim3(256), 0, st, hdr, qt, qo, 0);
   }
@@ -293,7 +313,7 @@ void launch_plan_tiles(const Common& c, const Layout& L, char* ws, const int32_t
     auto* kt = (pg::TileDesc*)(ws + L.kvtiles);
     int* ko = (int*)(ws + L.kvorder);
     const int blocks = (int)ceil_div_l(L.max_kv, 256);
-    hipLaunchKernelGGL(pg::plan_tiles_kernel, dim3(blocks), dim3(256), 0, st, cu_s, c.ng, pg::kFwdBM, pg::kKvBN,
+    hipLaunchKernelGGL(pg::plan_tiles_kernel, dim3(blocks), dim3(256), 0, st, cu_s, c.ng, pg::kFwdBM, L.bkv,
                        L.kv_chunks, L.split, (int)L.max_kv, hdr, gi, kvoff, kt, 1);
     hipLaunchKernelGGL(pg::plan_rank_kernel, dim3(blocks), dim3(256), 0, st, hdr, kt, ko, 1);
   }
@@ -307,7 +327,7 @@ void launch_fwd(const pg::FwdArgs& a, long max_q, hipStream_t st) {
 }
 
 template <typename T, int D>
-void launch_bwd(const pg::BwdArgs& a, long max_q, long max_kv, hipStream_t st) {
+void launch_bwd(const pg::BwdArgs& a, long max_q, long max_kv, bool wide, hipStream_t st) {
   // dQ first: it also writes Dsum, which the dK/dV kernel reads
   if (max_q > 0) {
     Timed tm(PG_K_DQ, st);
@@ -318,7 +338,12 @@ void launch_bwd(const pg::BwdArgs& a, long max_q, long max_kv, hipStream_t st) {
     {
       Timed tm(PG_K_DKDV, st);
       const long blocks = pg::xcd_grid_blocks(max_kv, a.h_kv, 1);
-      hipLaunchKernelGGL((pg::dkdv_kernel<T, D>), dim3((unsigned)blocks), dim3(pg::kKvThreads), 0, st, a);
+      if (wide) {
+        if constexpr (sizeof(T) == 2)
+          hipLaunchKernelGGL((pg::dkdv_wide_kernel<D>), dim3((unsigned)blocks), dim3(pg::kWideThreads), 0, st, a);
+      } else {
+        hipLaunchKernelGGL((pg::dkdv_kernel<T, D>), dim3((unsigned)blocks), dim3(pg::kKvThreads), 0, st, a);
+      }
     }
     if (a.kv_chunks > 1 && a.total_prefix > 0) {
       Timed tm(PG_K_KV_REDUCE, st);
@@ -370,7 +395,8 @@ int fwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
 // out: dq_pre, dk_pre, dv_pre, dq_suf, dk_suf, dv_suf.
 int bwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const int32_t* gsz, const void* const* in,
              void* const* out, bool xl, void* workspace, size_t workspace_bytes, void* stream) {
-  const Layout L = make_layout(c.ng, c.ns, c.tp, c.ts, c.h_q, c.h_kv, c.d, true);
+  const bool wide = use_wide(c.dtype, c.ng, c.tp, c.ts, c.h_q, c.h_kv);
+  const Layout L = make_layout(c.ng, c.ns, c.tp, c.ts, c.h_q, c.h_kv, c.d, true, wide);
   if (!workspace || workspace_bytes < L.total)
     return fail(PG_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace_bytes, L.total);
   int rc = device_ready();
@@ -385,6 +411,7 @@ int bwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
   a.do_pre = in[10]; a.do_suf = in[11];
   a.dq_pre = out[0]; a.dk_pre = out[1]; a.dv_pre = out[2]; a.dq_suf = out[3]; a.dk_suf = out[4]; a.dv_suf = out[5];
   a.dsum = (float*)(ws + L.dsum);
+  a.lse2 = wide ? (float*)(ws + L.lse2) : nullptr;
   a.part = (float*)(ws + L.part);
   a.kv_chunks = L.kv_chunks;
   a.hdr = (const pg::PlanHeader*)(ws + L.hdr);
@@ -400,11 +427,11 @@ int bwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
   a.xl = xl ? 1 : 0;
   a.xrow = (const int*)(ws + L.xrow);
   if (c.dtype == PG_BF16) {
-    if (c.d == 128) launch_bwd<pg::bf16, 128>(a, L.max_q, L.max_kv, st);
-    else launch_bwd<pg::bf16, 64>(a, L.max_q, L.max_kv, st);
+    if (c.d == 128) launch_bwd<pg::bf16, 128>(a, L.max_q, L.max_kv, wide, st);
+    else launch_bwd<pg::bf16, 64>(a, L.max_q, L.max_kv, wide, st);
   } else {
-    if (c.d == 128) launch_bwd<float, 128>(a, L.max_q, L.max_kv, st);
-    else launch_bwd<float, 64>(a, L.max_q, L.max_kv, st);
+    if (c.d == 128) launch_bwd<float, 128>(a, L.max_q, L.max_kv, wide, st);
+    else launch_bwd<float, 64>(a, L.max_q, L.max_kv, wide, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "backward launch");
@@ -499,7 +526,8 @@ size_t pg_attn_bwd_workspace_size(int n_groups, int n_suffixes, int total_prefix
   if (n_groups < 0 || n_suffixes < 0 || total_prefix < 0 || total_suffix < 0 || h_q < 0 || h_kv < 0 ||
       head_dim < 0)
     return 0;
-  return make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, true).total;
+  return std::max(make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, true).total,
+                  make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, true, true).total);
 }
 
 const char* pg_status_string(int s) {

@@ -28,6 +28,7 @@ struct BwdArgs {
   const float *lse_pre, *lse_suf;
   void *dq_pre, *dk_pre, *dv_pre, *dq_suf, *dk_suf, *dv_suf;
   float* dsum;  // [h_q][total_prefix + total_suffix]
+  float* lse2;  // the same shape: lse in log2 units, for dkdv_wide_kernel
   float* part;  // [kv_chunks][2 (dK, dV)][total_prefix][h_kv][D] fp32 partials, when kv_chunks > 1
   int kv_chunks;
   const PlanHeader* hdr;
@@ -454,7 +455,11 @@ __global__ void __launch_bounds__(kDqThreads, 2) dq_kernel(const BwdArgs a) {
       for (int e = 0; e < 8; ++e) part = fmaf(E::frag_elem(of, e), E::frag_elem(gf[kk], e), part);
     }
     dsum = wave_swap32_sum(part);
-    if (qvalid && hh == 0) a.dsum[(size_t)head * rows_all + (suffix ? a.total_prefix : 0) + qrow] = dsum;
+    if (qvalid && hh == 0) {
+      const size_t at = (size_t)head * rows_all + (suffix ? a.total_prefix : 0) + qrow;
+      a.dsum[at] = dsum;
+      if (a.lse2) a.lse2[at] = lse2;
+    }
   }
   const int seg_q = suffix ? a.seg_start[qrow_c] : 0;
   const int seg_w_lo = (suffix && wave_active) ? a.seg_start[wq0] : 0;

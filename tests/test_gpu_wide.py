@@ -1,0 +1,44 @@
+"""GPU parity of the backward's 256-key dK/dV kernel at the edges of its tiles.
+
+The sizes are large enough for the library to choose that kernel (test_wide_codegen.py checks the choice) and
+ragged everywhere: prefixes one row past a key tile, responses shorter than a query tile, a key tile spanning
+several members, empty responses, a group without members, GQA ratios 1, 4 and 8, both head dims and both
+layouts. Tolerances are those of every bf16 parity test (tests/_parity.py).
+"""
+import numpy as np
+import pytest
+
+from paper_2506_05433_amd.inputs import make_problem
+from tests.test_gpu_parity import _full_compare
+from tests.test_gpu_xours import _run_both
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+RAGGED = (1, 33, 0, 700, 256, 511, 64, 31, 400, 90)
+CASES = [
+    # (lengths, h_q, h_kv, d, kv head compared)
+    (((1025,), (10,), RAGGED), 64, 8, 128, 5),
+    (((1025,), (10,), RAGGED), 64, 8, 64, 2),
+    (((1500, 1100), (10, 0), RAGGED), 64, 8, 128, 7),
+    (((1281, 1024), (3, 10), (257, 1, 3200) + RAGGED), 32, 32, 64, 31),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_wide_backward(case):
+    lengths, hq, hkv, d, kv = CASES[case]
+    prob = make_problem("single_group", seed=700 + case, lengths=lengths, h_q=hq, h_kv=hkv, head_dim=d,
+                        scale=1.0 / np.sqrt(d))
+    r = hq // hkv
+    _full_compare(prob, heads=list(range(kv * r, (kv + 1) * r)), kv_heads=[kv])
+
+
+def test_wide_backward_xours_and_repeat():
+    lengths, hq, hkv, d, _ = CASES[0]
+    prob = make_problem("single_group", seed=710, lengths=lengths, h_q=hq, h_kv=hkv, head_dim=d)
+    a, _ = _run_both(prob)
+    b, _ = _run_both(prob)
+    for n in a:
+        assert torch.equal(a[n], b[n]), f"{n} differs between two runs"
