@@ -52,6 +52,7 @@ struct Layout {
   long max_q, max_kv;
   int kv_chunks, split;
   int bkv;  // keys per key tile: kKvBN, or kWideBN for dkdv_wide_kernel
+  int bm;   // query rows per query tile: kFwdBM, or kWideBM for the 256-row kernels
 };
 
 // Pieces each prefix key tile's query walk is split into for the dK/dV kernel: enough
@@ -93,13 +94,25 @@ bool use_wide(int dtype, int ng, int tp, int ts, int h_q, int h_kv) {
   return walk * (double)ceil_div_l(tp, pg::kWideBN) * h_kv >= 80.0 * 256.0;
 }
 
-Layout make_layout(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d, bool bwd, bool wide = false) {
+// Whether the backward runs dq_wide_kernel (256-row query tiles). Its workgroups have a CU to themselves,
+// so loading their rows and storing dQ is not hidden: it needs long key walks, and enough tiles to give
+// every CU two. Measured (dq_kernel -> wide), one group of 16/4 or 32/8 heads: P 1024 1278 -> 1468 us, 4096
+// 2477 -> 2500 us, 8192 804 -> 770 us, 16384 4664 -> 4420 us. With 64-wide heads the vector work per
+// product doubles and one wave per SIMD cannot issue it (206 -> 278 us on prefixes of 179..2530).
+bool use_wide_q(int dtype, int ng, int tp, int ts, int h_q, int d) {
+  return dtype == PG_BF16 && d == 128 && ng > 0 && tp / 8192 >= ng &&
+         (ceil_div_l(tp, pg::kWideBM) + ceil_div_l(ts, pg::kWideBM)) * h_q >= 512;
+}
+
+Layout make_layout(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d, bool bwd, bool wide = false,
+                   bool wide_q = false) {
   Layout L{};
+  L.bm = wide_q ? pg::kWideBM : pg::kFwdBM;
   L.bkv = wide ? pg::kWideBN : pg::kKvBN;
   L.kv_chunks = bwd ? kv_chunks_for(ng, tp, ts, h_q, h_kv, L.bkv) : 1;
-  L.split = (ceil_div_l(tp, pg::kFwdBM) + ceil_div_l(ts, pg::kFwdBM) + ng) * (long)h_q < kSplitBelow ? 1 : 0;
+  L.split = !wide_q && (ceil_div_l(tp, pg::kFwdBM) + ceil_div_l(ts, pg::kFwdBM) + ng) * (long)h_q < kSplitBelow ? 1 : 0;
   // bounds of the tile lists in either tiling (splitting adds at most one tile per member)
-  L.max_q = ceil_div_l(tp, pg::kFwdBM) + ceil_div_l(ts, pg::kFwdBM) + 2L * ng + ns;
+  L.max_q = ceil_div_l(tp, L.bm) + ceil_div_l(ts, L.bm) + 2L * ng + ns;
   L.max_kv = bwd ? (ceil_div_l(tp, L.bkv) + ng) * L.kv_chunks + ceil_div_l(ts, L.bkv) + ng + ns : 0;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
@@ -273,7 +286,7 @@ int launch_plan(const Common& c, const Layout& L, char* ws, const int32_t* cu_p,
   if (one_block) {
     // every tile list fits one block: groups, tiles and ranks in one launch
     hipLaunchKernelGGL(pg::plan_fused_kernel, dim3(1), dim3(pg::kPlanThreads), 0, st, cu_p, cu_s, gsz, c.ng, c.ns,
-                       c.tp, c.ts, pg::kFwdBM, L.bkv, L.kv_chunks, L.split, L.max_q,
+                       c.tp, c.ts, L.bm, L.bkv, L.kv_chunks, L.split, L.max_q,
                        bwd ? L.max_kv : 0x7fffffffL, hdr, gi, qoff, kvoff, qt, qo,
                        bwd ? (pg::TileDesc*)(ws + L.kvtiles) : nullptr, (int*)(ws + L.kvorder),
                        fused_seg ? (int*)(ws + L.seg) : nullptr);
@@ -299,13 +312,13 @@ void launch_plan_tiles(const Common& c, const Layout& L, char* ws, const int32_t
   int* qoff = (int*)(ws + L.qoff);
   int* kvoff = (int*)(ws + L.kvoff);
   hipLaunchKernelGGL(pg::plan_groups_kernel, dim3(1), dim3(pg::kPlanThreads), 0, st, cu_p, cu_s, gsz, c.ng, c.ns,
-                     c.tp, c.ts, pg::kFwdBM, L.bkv, L.kv_chunks, L.split, L.max_q, bwd ? L.max_kv : 0x7fffffffL,
+                     c.tp, c.ts, L.bm, L.bkv, L.kv_chunks, L.split, L.max_q, bwd ? L.max_kv : 0x7fffffffL,
                      hdr, gi, qoff, kvoff);
   auto* qt = (pg::TileDesc*)(ws + L.qtiles);
   int* qo = (int*)(ws + L.qorder);
   if (L.max_q > 0) {
     const int blocks = (int)ceil_div_l(L.max_q, 256);
-    hipLaunchKernelGGL(pg::plan_tiles_kernel, dim3(blocks), dim3(256), 0, st, cu_s, c.ng, pg::kFwdBM, L.bkv,
+    hipLaunchKernelGGL(pg::plan_tiles_kernel, dim3(blocks), dim3(256), 0, st, cu_s, c.ng, L.bm, L.bkv,
                        1, L.split, (int)L.max_q, hdr, gi, qoff, qt, 0);
     hipLaunchKernelGGL(pg::plan_rank_kernel, dim3(blocks), dim3(256), 0, st, hdr, qt, qo, 0);
   }
@@ -313,7 +326,7 @@ void launch_plan_tiles(const Common& c, const Layout& L, char* ws, const int32_t
     auto* kt = (pg::TileDesc*)(ws + L.kvtiles);
     int* ko = (int*)(ws + L.kvorder);
     const int blocks = (int)ceil_div_l(L.max_kv, 256);
-    hipLaunchKernelGGL(pg::plan_tiles_kernel, dim3(blocks), dim3(256), 0, st, cu_s, c.ng, pg::kFwdBM, L.bkv,
+    hipLaunchKernelGGL(pg::plan_tiles_kernel, dim3(blocks), dim3(256), 0, st, cu_s, c.ng, L.bm, L.bkv,
                        L.kv_chunks, L.split, (int)L.max_kv, hdr, gi, kvoff, kt, 1);
     hipLaunchKernelGGL(pg::plan_rank_kernel, dim3(blocks), dim3(256), 0, st, hdr, kt, ko, 1);
   }
@@ -327,12 +340,17 @@ void launch_fwd(const pg::FwdArgs& a, long max_q, hipStream_t st) {
 }
 
 template <typename T, int D>
-void launch_bwd(const pg::BwdArgs& a, long max_q, long max_kv, bool wide, hipStream_t st) {
+void launch_bwd(const pg::BwdArgs& a, long max_q, long max_kv, int bm, bool wide, hipStream_t st) {
   // dQ first: it also writes Dsum, which the dK/dV kernel reads
   if (max_q > 0) {
     Timed tm(PG_K_DQ, st);
     const long blocks = pg::xcd_grid_blocks(max_q, a.h_q, a.h_q / a.h_kv);
-    hipLaunchKernelGGL((pg::dq_kernel<T, D>), dim3((unsigned)blocks), dim3(pg::kDqThreads), 0, st, a);
+    if (bm == pg::kWideBM) {
+      if constexpr (sizeof(T) == 2 && D == 128)
+        hipLaunchKernelGGL((pg::dq_wide_kernel<D>), dim3((unsigned)blocks), dim3(pg::kWideThreads), 0, st, a);
+    } else {
+      hipLaunchKernelGGL((pg::dq_kernel<T, D>), dim3((unsigned)blocks), dim3(pg::kDqThreads), 0, st, a);
+    }
   }
   if (max_kv > 0) {
     {
@@ -396,7 +414,8 @@ int fwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
 int bwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const int32_t* gsz, const void* const* in,
              void* const* out, bool xl, void* workspace, size_t workspace_bytes, void* stream) {
   const bool wide = use_wide(c.dtype, c.ng, c.tp, c.ts, c.h_q, c.h_kv);
-  const Layout L = make_layout(c.ng, c.ns, c.tp, c.ts, c.h_q, c.h_kv, c.d, true, wide);
+  const Layout L = make_layout(c.ng, c.ns, c.tp, c.ts, c.h_q, c.h_kv, c.d, true, wide,
+                               use_wide_q(c.dtype, c.ng, c.tp, c.ts, c.h_q, c.d));
   if (!workspace || workspace_bytes < L.total)
     return fail(PG_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace_bytes, L.total);
   int rc = device_ready();
@@ -427,11 +446,11 @@ int bwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
   a.xl = xl ? 1 : 0;
   a.xrow = (const int*)(ws + L.xrow);
   if (c.dtype == PG_BF16) {
-    if (c.d == 128) launch_bwd<pg::bf16, 128>(a, L.max_q, L.max_kv, wide, st);
-    else launch_bwd<pg::bf16, 64>(a, L.max_q, L.max_kv, wide, st);
+    if (c.d == 128) launch_bwd<pg::bf16, 128>(a, L.max_q, L.max_kv, L.bm, wide, st);
+    else launch_bwd<pg::bf16, 64>(a, L.max_q, L.max_kv, L.bm, wide, st);
   } else {
-    if (c.d == 128) launch_bwd<float, 128>(a, L.max_q, L.max_kv, wide, st);
-    else launch_bwd<float, 64>(a, L.max_q, L.max_kv, wide, st);
+    if (c.d == 128) launch_bwd<float, 128>(a, L.max_q, L.max_kv, L.bm, wide, st);
+    else launch_bwd<float, 64>(a, L.max_q, L.max_kv, L.bm, wide, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "backward launch");

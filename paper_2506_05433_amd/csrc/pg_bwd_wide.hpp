@@ -1,7 +1,7 @@
-// dK, dV of large bf16 problems (key-stationary, like dkdv_kernel): 256 keys per workgroup, 64 per
-// wave, one wave per SIMD with all 512 registers.
+// The backward of large bf16 problems: dkdv_wide_kernel (256 keys per workgroup, 64 per wave) and
+// dq_wide_kernel (256 query rows per workgroup, 64 per wave), one wave per SIMD with all 512 registers.
 //
-// What bounds it: the chip's power. On N(0,1) data a loop of nothing but 32x32x16 products reaches
+// What bounds them: the chip's power. On N(0,1) data a loop of nothing but 32x32x16 products reaches
 // 1841 TFLOP/s (the clock falls to 1.76 GHz); with one LDS operand fragment read per product it
 // reaches 1461, with one per two products 1590. dkdv_kernel reads one per product, hands P from one
 // wave to another through LDS and walks every query tile once per 128 keys. Here a fragment serves
@@ -21,122 +21,15 @@
 // P beside dP and dS beside dV only (3% slower: the vector work does not fit those phases); two wait
 // states before every product instead of before the first that reads new operands (2% slower).
 #pragma once
-#include <type_traits>
-
 #include "pg_bwd.hpp"
+#include "pg_wide.hpp"
 
 namespace pg {
 
-// Accumulators pinned in AGPRs. The products below name their accumulator registers themselves and
-// declare every AGPR clobbered, so the compiler keeps nothing of its own there between them. R is
-// the first of the 16 registers. The compiler knows neither that these are matrix instructions nor
-// their hazards: FRESH puts the two wait states a vector write of an operand needs before the first
-// product that reads it (later ones are further away), and acc_settle() comes before the first
-// acc_read(). tests/test_wide_codegen.py checks both rules in the generated code.
-#define PG_ALL_AGPRS "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", "a10", "a11", "a12", "a13", "a14", "a15", "a16", "a17", "a18", "a19", "a20", "a21", "a22", "a23", "a24", "a25", "a26", "a27", "a28", "a29", "a30", "a31", "a32", "a33", "a34", "a35", "a36", "a37", "a38", "a39", "a40", "a41", "a42", "a43", "a44", "a45", "a46", "a47", "a48", "a49", "a50", "a51", "a52", "a53", "a54", "a55", "a56", "a57", "a58", "a59", "a60", "a61", "a62", "a63", "a64", "a65", "a66", "a67", "a68", "a69", "a70", "a71", "a72", "a73", "a74", "a75", "a76", "a77", "a78", "a79", "a80", "a81", "a82", "a83", "a84", "a85", "a86", "a87", "a88", "a89", "a90", "a91", "a92", "a93", "a94", "a95", "a96", "a97", "a98", "a99", "a100", "a101", "a102", "a103", "a104", "a105", "a106", "a107", "a108", "a109", "a110", "a111", "a112", "a113", "a114", "a115", "a116", "a117", "a118", "a119", "a120", "a121", "a122", "a123", "a124", "a125", "a126", "a127", "a128", "a129", "a130", "a131", "a132", "a133", "a134", "a135", "a136", "a137", "a138", "a139", "a140", "a141", "a142", "a143", "a144", "a145", "a146", "a147", "a148", "a149", "a150", "a151", "a152", "a153", "a154", "a155", "a156", "a157", "a158", "a159", "a160", "a161", "a162", "a163", "a164", "a165", "a166", "a167", "a168", "a169", "a170", "a171", "a172", "a173", "a174", "a175", "a176", "a177", "a178", "a179", "a180", "a181", "a182", "a183", "a184", "a185", "a186", "a187", "a188", "a189", "a190", "a191", "a192", "a193", "a194", "a195", "a196", "a197", "a198", "a199", "a200", "a201", "a202", "a203", "a204", "a205", "a206", "a207", "a208", "a209", "a210", "a211", "a212", "a213", "a214", "a215", "a216", "a217", "a218", "a219", "a220", "a221", "a222", "a223", "a224", "a225", "a226", "a227", "a228", "a229", "a230", "a231", "a232", "a233", "a234", "a235", "a236", "a237", "a238", "a239", "a240", "a241", "a242", "a243", "a244", "a245", "a246", "a247", "a248", "a249", "a250", "a251", "a252", "a253", "a254", "a255"
-template <int R, bool FRESH>
-__device__ __forceinline__ void mma_acc(const bf16x8& a, const bf16x8& b) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  if constexpr (FRESH)
-    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 a[%0:%1], %2, %3, a[%0:%1]" ::"n"(R), "n"(R + 15), "v"(a), "v"(b)
-                 : PG_ALL_AGPRS);
-  else
-    asm volatile("v_mfma_f32_32x32x16_bf16 a[%0:%1], %2, %3, a[%0:%1]" ::"n"(R), "n"(R + 15), "v"(a), "v"(b)
-                 : PG_ALL_AGPRS);
-#endif
-}
-template <int R>
-__device__ __forceinline__ void acc_zero() {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("v_accvgpr_write_b32 a[%0], 0" ::"n"(R) : PG_ALL_AGPRS);
-#endif
-}
-template <int R>
-__device__ __forceinline__ float acc_read() {
-  float v = 0.f;
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(v) : "n"(R));
-#endif
-  return v;
-}
-__device__ __forceinline__ void acc_settle() {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_nop 15\n\ts_nop 15" ::: PG_ALL_AGPRS);
-#endif
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (N > 0) {
-    static_for<N - 1>(f);
-    f(std::integral_constant<int, N - 1>{});
-  }
-}
-
-#define PG_INLINE __attribute__((always_inline))
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-// 16 (or 4) bytes per lane from a buffer into LDS at byte `lds` + 16 (4) * lane, issued in asm so
-// that the compiler does not make every later LDS read wait for it: the caller waits (wait_vm)
-// and meets a barrier before anybody reads the bytes.
-__device__ __forceinline__ void dma16(u32x4 rs, unsigned lds, int voff) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "memory");
-#endif
-}
-__device__ __forceinline__ void dma4(u32x4 rs, unsigned lds, int voff) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rs) : "memory");
-#endif
-}
-__device__ __forceinline__ void block_meet() {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_barrier" ::: "memory");
-#endif
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-#endif
-}
-__device__ __forceinline__ u32x4 make_rsrc(const void* p, int bytes) {
-  const uint64_t a = (uint64_t)p;
-  u32x4 r;
-  r[0] = uniform((int)(unsigned)a);
-  r[1] = uniform((int)(unsigned)(a >> 32)) & 0xffff;
-  r[2] = uniform(bytes);
-  r[3] = 0x00020000;
-  return r;
-}
-__device__ __forceinline__ unsigned lds_addr(const void* p) {
-  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
-}
-
-// Two floats rounded to bf16, kept where the call stands: left to itself the compiler gathers the
-// conversions of a phase at its end, where no matrix instruction is in flight to hide them.
-__device__ __forceinline__ unsigned pack_bf16(float x, float y) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 v = {(bf16)x, (bf16)y};
-  unsigned u = __builtin_bit_cast(unsigned, v);
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("" : "+v"(u));
-#endif
-  return u;
-}
-
-// cond ? a : b on values: on captured variables the operator selects between their addresses, which
-// keeps the whole closure in memory
-template <typename V>
-__device__ __forceinline__ V pick(bool cond, V a, V b) { return cond ? a : b; }
-
-constexpr int kWideThreads = 256;
 constexpr int kWideKeys = 64;                    // keys per wave
 constexpr int kWideBN = 4 * kWideKeys;           // keys per workgroup
 constexpr int kWideBQ = 32;                      // query rows per staged tile
 
-template <int N>
-using Int = std::integral_constant<int, N>;
 constexpr int kDenseRow = 1 << 30;  // stands for a row that sees every key
 
 template <int D>
@@ -517,6 +410,318 @@ __global__ void __launch_bounds__(kWideThreads, 1) dkdv_wide_kernel(const BwdArg
       const f32x4 x = f32x4{acc_read<R>() * sc, acc_read<R + 1>() * sc, acc_read<R + 2>() * sc, acc_read<R + 3>() * sc};
       if (td.nchunks > 1) *(f32x4*)(part + d0) = x;
       else E::store4(out + d0, x[0], x[1], x[2], x[3]);
+    });
+  });
+}
+
+
+// ------------------------------------------------------------------ dQ (query-stationary)
+// Per 32-key tile and wave: S^T = K Q^T and dP^T = V dO^T (keys x 64 queries), dQ^T += K^T dS^T. Q and dO
+// stay in AGPRs beside the accumulators, which leaves the VGPRs to two tiles' P and dP: the matrix
+// products of a tile then run beside the vector work of the one before. One wave per SIMD is bound by
+// the instructions it issues (about 4.5 clocks each), so dP's accumulator starts at -Dsum instead of
+// subtracting it per element (that alone 146.5 -> 142.4 ms on the case below), and P and dP alternate
+// between two sets of registers in a loop unrolled by two, so that nothing is copied.
+// Measured on 8 groups x 16 members, P 1246..26888, 64/8 heads: 154.2 -> 142.4 ms (1274 TFLOP/s of its three
+// products; matrix cores 64% busy at 1.91 GHz, before 66% at 1.73); 1 x 16, P 16384, 32/8: 4.66 -> 4.42 ms.
+template <int D>
+__global__ void __launch_bounds__(kWideThreads, 1) dq_wide_kernel(const BwdArgs a) {
+  using T = bf16;
+  using E = Elt<bf16>;
+  using Frag = E::Frag;
+  using Copies = KvCopies<D>;
+  constexpr int BN = kWideBK;
+  constexpr int KK = D / 16, DB = D / 32;
+  constexpr int NBUF = 4;
+  constexpr int PF = D == 128 ? 3 : 2;  // row fragments read ahead of their products
+  constexpr int AHEAD = 3;              // transposed fragments read ahead
+  // AGPRs: dQ^T blocks (qb, db) from a0, then the B operands Q and dO
+  constexpr int RQ = 32 * DB, RG = RQ + 8 * KK;
+  constexpr int PB = 5;                 // pairs of P beside dQ, the rest beside dP
+  constexpr int TILE = Copies::TILE, STAGE = Copies::STAGE, PW = Copies::PW;
+  __shared__ __attribute__((aligned(1024))) char stage[NBUF * STAGE];
+
+  const BlockSlot slot = xcd_slot(blockIdx.x, a.h_q, a.h_q / a.h_kv);
+  const int rank = uniform(slot.unit), head = uniform(slot.head);
+  if (rank >= a.hdr->n_qtiles) return;
+  const TileDesc* tp = a.qtiles + uniform(a.qorder[rank]);
+  const GroupInfoEx* gp = a.ginfo + uniform(tp->group);
+  const int row0 = uniform(tp->row0), row1 = uniform(tp->row1), aux = uniform(tp->aux);
+  const bool suffix = uniform(tp->kind) == 1;
+  const int g_p0 = uniform(gp->p0), g_p1 = uniform(gp->p1), g_s0 = uniform(gp->s0);
+  const int kvh = uniform(head / (a.h_q / a.h_kv));
+  const int rows_all = a.total_prefix + a.total_suffix;
+  const int xo_pre = a.xl ? g_s0 : 0, xo_suf = a.xl ? g_p1 : 0;
+  const int xq = suffix ? xo_suf : xo_pre;
+
+  const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
+  const int n = lane & 31, hh = lane >> 5;
+  const int wq0 = row0 + 64 * wave;
+  const bool wave_active = wq0 < row1;
+  const int wq1 = min(wq0 + 64, row1) - 1;
+
+  const int kA0 = g_p0, kA1 = suffix ? g_p1 : row1;
+  const int kB0 = suffix ? aux : 0, kB1 = suffix ? row1 : 0;
+  const int nA = (kA1 - kA0 + BN - 1) / BN, nB = (kB1 - kB0 + BN - 1) / BN;
+  const int ntiles = nA + nB;
+  const int kvstride = a.h_kv * D;
+  Copies cp;
+  {
+    const T* p = (const T*)(wave < 2 ? a.k_pre : a.v_pre) + (size_t)(kA0 + xo_pre) * kvstride + kvh * D;
+    const T* q = (const T*)(wave < 2 ? a.k_suf : a.v_suf) + (size_t)(kB0 + xo_suf) * kvstride + kvh * D;
+    cp.init(stage, p, kA1 - kA0, q, kB1 - kB0, kvstride, wave, lane);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      if (b > 0) cp.next();
+#pragma unroll
+      for (int k = 0; k < PW; ++k) cp.part(k, b * STAGE);
+    }
+  }
+
+  int qrow_c[2], seg_q[2];
+  bool qvalid[2];
+  float lse2[2];
+  f32x16 ndsum[2];  // -Dsum of the lane's query in every register: what dP starts at
+  static_for<32 * DB>([](auto r) { acc_zero<decltype(r)::value>(); });
+  static_for<2>([&](auto b_) PG_INLINE {
+    constexpr int qb = decltype(b_)::value;
+    const int qrow = wq0 + 32 * qb + n;
+    qvalid[qb] = qrow < row1;
+    qrow_c[qb] = qvalid[qb] ? qrow : row1 - 1;
+    const size_t off = ((size_t)(qrow_c[qb] + xq) * a.h_q + head) * D + 8 * hh;
+    const T* Q = (const T*)(suffix ? a.q_suf : a.q_pre) + off;
+    const T* G = (const T*)(suffix ? a.do_suf : a.do_pre) + off;
+    const T* O = (const T*)(suffix ? a.o_suf : a.o_pre) + off;
+    float part = 0.f;
+    Frag qf[KK], gf[KK], of[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      qf[kk] = E::global_row(Q + 16 * kk, qvalid[qb]);
+      gf[kk] = E::global_row(G + 16 * kk, qvalid[qb]);
+      of[kk] = E::global_row(O + 16 * kk, qvalid[qb]);
+    }
+    static_for<KK>([&](auto k) PG_INLINE {
+      constexpr int kk = decltype(k)::value;
+      acc_put_frag<RQ + 4 * (KK * qb + kk)>(qf[kk]);
+      acc_put_frag<RG + 4 * (KK * qb + kk)>(gf[kk]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) part = fmaf(E::frag_elem(of[kk], e), E::frag_elem(gf[kk], e), part);
+    });
+    const float* L = suffix ? a.lse_suf : a.lse_pre;
+    const int ld = a.xl ? rows_all : (suffix ? a.total_suffix : a.total_prefix);
+    lse2[qb] = L[(size_t)head * ld + qrow_c[qb] + xq] * kLog2e;
+    const float dsum = wave_swap32_sum(part);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ndsum[qb][r] = -dsum;
+    if (qvalid[qb] && hh == 0) {  // for the dK/dV kernel
+      const size_t at = (size_t)head * rows_all + (suffix ? a.total_prefix : 0) + qrow;
+      a.dsum[at] = dsum;
+      if (a.lse2) a.lse2[at] = lse2[qb];
+    }
+    seg_q[qb] = suffix ? a.seg_start[qrow_c[qb]] : 0;
+  });
+  const int seg_lo = uniform((suffix && wave_active) ? a.seg_start[wq0] : 0);
+  const int seg_hi = uniform((suffix && wave_active) ? a.seg_start[wq1] : 0);
+  const float c = a.scale_log2;
+  FragOffsets<T, D> fo;
+  fo.init(lane);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+
+  // the tile being worked on: its first key, the end of its run, and whether it is of the first run
+  int k0 = nA > 0 ? kA0 : kB0, kend = nA > 0 ? kA1 : kB1;
+  bool seg_a = nA > 0;
+  int off = 0, off_p = 0;
+  bool skip = false, full = true;
+  auto visibility = [&]() PG_INLINE {
+    const bool cross = seg_a & suffix;  // response rows x prefix keys: no causal limit
+    skip = !wave_active | (!cross & (k0 > wq1)) | (!seg_a & (k0 + BN <= seg_lo));
+    full = (k0 + BN <= kend) & (cross | (k0 + BN - 1 <= wq0)) & (seg_a | (k0 >= seg_hi));
+  };
+  visibility();
+  Frag kr[KK];
+#pragma unroll
+  for (int kk = 0; kk < PF; ++kk) kr[kk] = fo.row(stage, 0, kk);
+  // P and dP - Dsum of this tile and of the one before (they alternate)
+  f32x16 sb[2][2] = {}, db_[2][2] = {};
+
+  // One step: S of tile j beside dS of the tile before, dQ of the tile before beside P of tile j, and
+  // dP of tile j beside the rest of P.
+  auto step = [&](auto b_, auto prev_, auto cur_) PG_INLINE {
+    constexpr bool PREV = decltype(prev_)::value, CUR = decltype(cur_)::value;
+    f32x16(&s)[2] = sb[decltype(b_)::value];
+    f32x16(&p_prev)[2] = sb[1 - decltype(b_)::value];
+    f32x16(&dp)[2] = db_[decltype(b_)::value];
+    f32x16(&dp_prev)[2] = db_[1 - decltype(b_)::value];
+    const char* Kt = stage + off;
+    const char* Vt = Kt + TILE;
+    const char* Kp = stage + off_p;
+    const int off_n = off == (NBUF - 1) * STAGE ? 0 : off + STAGE;
+    const int off_w = off_n == (NBUF - 1) * STAGE ? 0 : off_n + STAGE;
+    const int off_c = off_w == (NBUF - 1) * STAGE ? 0 : off_w + STAGE;
+    const int k0_it = k0, kend_it = kend;
+    const bool seg_it = seg_a;
+    auto advance = [&]() PG_INLINE {
+      k0 += BN;
+      if (__builtin_expect(k0 >= kend, 0)) {
+        asm volatile("");
+        k0 = kB0;
+        kend = kB1;
+        seg_a = false;
+      }
+    };
+    u32x4 ds[2][2];
+    Frag vr[KK], kt[2 * DB];
+    auto k_tr = [&](auto k) PG_INLINE {
+      constexpr int i = decltype(k)::value;
+      if constexpr (i < 2 * DB) kt[i] = fo.tr(Kp, i / DB, i % DB);
+    };
+    auto p_pair = [&](auto k) PG_INLINE {
+      constexpr int p = decltype(k)::value, i = p / 4, qb = p / 2 % 2, r = 4 * i + 2 * (p % 2);
+      s[qb][r] = fast_exp2(fmaf(s[qb][r], c, -lse2[qb]));
+      s[qb][r + 1] = fast_exp2(fmaf(s[qb][r + 1], c, -lse2[qb]));
+    };
+    auto d_pair = [&](auto k) PG_INLINE {
+      constexpr int p = decltype(k)::value, i = p / 4, qb = p / 2 % 2, r = 4 * i + 2 * (p % 2);
+      ds[qb][r / 8][r % 8 / 2] = pack_bf16(p_prev[qb][r] * dp_prev[qb][r], p_prev[qb][r + 1] * dp_prev[qb][r + 1]);
+    };
+    if constexpr (CUR) {
+      static_for<2 * KK>([&](auto x_) PG_INLINE {
+        constexpr int x = decltype(x_)::value, kk = x / 2;
+        if constexpr (x % 2 == 0) {
+          if constexpr (kk + PF < KK) kr[kk + PF] = fo.row(Kt, 0, kk + PF);
+          if constexpr (kk >= KK - AHEAD) k_tr(Int<kk - (KK - AHEAD)>{});
+        }
+        mma_v<RQ + 4 * (KK * (x % 2) + kk), kk == 0>(s[x % 2], kr[kk]);
+        if constexpr (x == 1) advance();
+        if constexpr (x == 3) cp.next();
+        constexpr int p0 = x < 2 ? 0 : 8 * (x - 2) / (2 * KK - 2), p1 = x < 2 ? 0 : 8 * (x - 1) / (2 * KK - 2);
+        static_for<p1 - p0>([&](auto y) PG_INLINE { d_pair(Int<p0 + decltype(y)::value>{}); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if (__builtin_expect(!full, 0)) {
+        settle(s[0], s[1]);
+        const int base = k0_it + 4 * hh;
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          int hi = kend_it - base;
+          if (!(seg_it & suffix)) hi = min(hi, qrow_c[qb] + 1 - base);
+          const int lo = seg_it ? -(1 << 30) : seg_q[qb] - base;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int o = 8 * (r >> 2) + (r & 3);
+            s[qb][r] = ((o >= lo) & (o < hi)) ? s[qb][r] : -INFINITY;
+          }
+        }
+      }
+    } else {
+      advance();
+      cp.next();
+      if constexpr (PREV) {
+        static_for<AHEAD>([&](auto k) PG_INLINE { k_tr(k); });
+        settle(dp_prev[0], dp_prev[1]);
+        static_for<16>([&](auto k) PG_INLINE { d_pair(k); });
+      }
+    }
+    if constexpr (PREV) {
+      // dQ^T += K^T dS of the tile before
+      static_for<4 * DB>([&](auto x_) PG_INLINE {
+        constexpr int x = decltype(x_)::value, I = x / 2, t = I / DB, db = I % DB;
+        if constexpr (x % 2 == 0) {
+          k_tr(Int<I + AHEAD>{});
+          if constexpr (CUR && I >= 2 * DB - PF) vr[I - (2 * DB - PF)] = fo.row(Vt, 0, I - (2 * DB - PF));
+        }
+        mma_acc<16 * (DB * (x % 2) + db), db == 0>(kt[I], __builtin_bit_cast(Frag, ds[x % 2][t]));
+        if constexpr (CUR && t == 0) {
+          constexpr int p0 = 8 + 8 * x / (2 * DB), p1 = 8 + 8 * (x + 1) / (2 * DB);
+          static_for<p1 - p0>([&](auto y) PG_INLINE { d_pair(Int<p0 + decltype(y)::value>{}); });
+        } else if constexpr (CUR) {
+          constexpr int p0 = PB * (x - 2 * DB) / (2 * DB), p1 = PB * (x - 2 * DB + 1) / (2 * DB);
+          static_for<p1 - p0>([&](auto y) PG_INLINE { p_pair(Int<p0 + decltype(y)::value>{}); });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    // publishes tile j + 1 and frees the stage of tile j - 1 for the copies of tile j + 3
+    wait_vm<PW>();
+    block_meet();
+    if constexpr (CUR) {
+      static_for<2 * KK>([&](auto x_) PG_INLINE {
+        constexpr int x = decltype(x_)::value, kk = x / 2;
+        if constexpr (x % 2 == 0) {
+          if constexpr (kk + PF < KK) vr[kk + PF] = fo.row(Vt, 0, kk + PF);
+          if constexpr (kk >= KK - PF) kr[kk - (KK - PF)] = fo.row(stage + off_n, 0, kk - (KK - PF));
+        }
+        if constexpr (kk == 0) mma_v_from<RG + 4 * KK * (x % 2)>(dp[x % 2], vr[0], ndsum[x % 2]);
+        else mma_v<RG + 4 * (KK * (x % 2) + kk), false>(dp[x % 2], vr[kk]);
+        constexpr int p0 = PB + (16 - PB) * x / (2 * KK), p1 = PB + (16 - PB) * (x + 1) / (2 * KK);
+        static_for<p1 - p0>([&](auto y) PG_INLINE { p_pair(Int<p0 + decltype(y)::value>{}); });
+        if constexpr (x % 2 == 0 && kk < PW) cp.part(kk, off_c);
+        if constexpr (x == 2 * KK - 2) visibility();
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      static_assert(PW <= KK, "every copy has its step");
+      off_p = off;
+    } else {
+#pragma unroll
+      for (int k = 0; k < PW; ++k) cp.part(k, off_c);
+#pragma unroll
+      for (int kk = 0; kk < PF; ++kk) kr[kk] = fo.row(stage + off_n, 0, kk);
+      visibility();
+      // the next tile worked on has no tile before it: P = 0 gives dS = 0, against its own K rows
+      s[0] = f32x16{}; s[1] = f32x16{};
+      dp[0] = f32x16{}; dp[1] = f32x16{};
+      off_p = off_n;
+    }
+    off = off_n;
+  };
+  bool prev = false;
+  auto visit = [&](auto b_) PG_INLINE {
+    const bool cur = !skip;
+    if (__builtin_expect(cur, 1)) step(b_, std::true_type{}, std::true_type{});
+    else if (prev) step(b_, std::true_type{}, std::false_type{});
+    else step(b_, std::false_type{}, std::false_type{});
+    prev = cur;
+  };
+  for (int j = 0; j < ntiles; j += 2) {
+    visit(Int<0>{});
+    if (j + 1 < ntiles) visit(Int<1>{});
+  }
+  if (prev) {  // dS and dQ of the last tile
+    settle(db_[0][0], db_[0][1]);
+    settle(db_[1][0], db_[1][1]);
+    f32x16 p_last[2] = {sb[0][0], sb[0][1]};
+    if (ntiles % 2 == 0) { p_last[0] = sb[1][0]; p_last[1] = sb[1][1]; }
+    f32x16 dp[2] = {db_[0][0], db_[0][1]};
+    if (ntiles % 2 == 0) { dp[0] = db_[1][0]; dp[1] = db_[1][1]; }
+    Frag dsf[2][2];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dp[qb][r] *= p_last[qb][r];
+      dsf[qb][0] = E::acc_to_frag(dp[qb], 0);
+      dsf[qb][1] = E::acc_to_frag(dp[qb], 1);
+    }
+    static_for<2 * DB>([&](auto i) PG_INLINE {
+      constexpr int I = decltype(i)::value, t = I / DB, db = I % DB;
+      const Frag k = fo.tr(stage + off_p, t, db);
+      mma_acc<16 * db, true>(k, dsf[0][t]);
+      mma_acc<16 * (DB + db), true>(k, dsf[1][t]);
+    });
+  }
+  wait_vm<0>();  // no copy may land after the workgroup's LDS is given back
+  acc_settle();
+  if (!wave_active) return;
+  static_for<2>([&](auto b) {
+    constexpr int qb = decltype(b)::value;
+    if (!qvalid[qb]) return;
+    T* out = (T*)(suffix ? a.dq_suf : a.dq_pre) + ((size_t)(wq0 + 32 * qb + n + xq) * a.h_q + head) * D;
+    static_for<DB * 4>([&](auto q) {
+      constexpr int db = decltype(q)::value / 4, i = decltype(q)::value % 4;
+      constexpr int R = 16 * (qb * DB + db) + 4 * i;
+      const float sc = a.scale;
+      E::store4(out + 32 * db + 8 * i + 4 * hh, acc_read<R>() * sc, acc_read<R + 1>() * sc, acc_read<R + 2>() * sc,
+                acc_read<R + 3>() * sc);
     });
   });
 }

@@ -1,6 +1,6 @@
-"""GPU parity of the backward's 256-key dK/dV kernel at the edges of its tiles.
+"""GPU parity of the backward's 256-key dK/dV and 256-row dQ kernels at the edges of their tiles.
 
-The sizes are large enough for the library to choose that kernel (test_wide_codegen.py checks the choice) and
+The sizes are large enough for the library to choose them (test_wide_codegen.py checks the choice) and
 ragged everywhere: prefixes one row past a key tile, responses shorter than a query tile, a key tile spanning
 several members, empty responses, a group without members, GQA ratios 1, 4 and 8, both head dims and both
 layouts. Tolerances are those of every bf16 parity test (tests/_parity.py).
@@ -25,18 +25,25 @@ CASES = [
     (((1281, 1024), (3, 10), (257, 1, 3200) + RAGGED), 32, 32, 64, 31),
 ]
 
+# the dQ kernel as well: prefixes of 8192 rows and more
+DQ_CASES = [
+    (((8193,), (10,), RAGGED), 16, 16, 128, 3),
+    (((8192, 8479), (0, 11), (5,) + RAGGED), 16, 8, 128, 6),
+]
 
-@pytest.mark.parametrize("case", range(len(CASES)))
+
+@pytest.mark.parametrize("case", range(len(CASES) + len(DQ_CASES)))
 def test_wide_backward(case):
-    lengths, hq, hkv, d, kv = CASES[case]
+    lengths, hq, hkv, d, kv = (CASES + DQ_CASES)[case]
     prob = make_problem("single_group", seed=700 + case, lengths=lengths, h_q=hq, h_kv=hkv, head_dim=d,
                         scale=1.0 / np.sqrt(d))
     r = hq // hkv
     _full_compare(prob, heads=list(range(kv * r, (kv + 1) * r)), kv_heads=[kv])
 
 
-def test_wide_backward_xours_and_repeat():
-    lengths, hq, hkv, d, _ = CASES[0]
+@pytest.mark.parametrize("which", [CASES[0], DQ_CASES[1]], ids=["dkdv", "dq"])
+def test_wide_backward_xours_and_repeat(which):
+    lengths, hq, hkv, d, _ = which
     prob = make_problem("single_group", seed=710, lengths=lengths, h_q=hq, h_kv=hkv, head_dim=d)
     a, _ = _run_both(prob)
     b, _ = _run_both(prob)

@@ -11,9 +11,9 @@ import subprocess
 import pytest
 
 from paper_2506_05433_amd import build as pg_build
-from tests.test_gpu_wide import CASES
+from tests.test_gpu_wide import CASES, DQ_CASES
 
-KERNELS = ("dkdv_wide_kernel",)
+KERNELS = ("dkdv_wide_kernel", "dq_wide_kernel")
 
 
 @pytest.fixture(scope="module")
@@ -42,8 +42,11 @@ def _regs(op):
 
 
 def hazards(lines):
-    """(compiler's own AGPR or scratch instructions, operand written too close before its product)."""
-    own, close, in_asm, recent = [], [], False, []
+    """(the compiler's own AGPR or scratch instructions, pinned products whose operand was written or whose result is
+    touched too soon). A product's VGPR operand may not be written by a vector instruction in the two issue slots
+    before it, and its VGPR result not be read or written by another kind of instruction for 11 slots (an 8-pass
+    product; one that follows it takes 8 slots)."""
+    own, close, in_asm, recent, results = [], [], False, [], []
     for line in lines:
         s = line.strip()
         if "ASMSTART" in s or "ASMEND" in s:
@@ -58,21 +61,31 @@ def hazards(lines):
         args = [a.strip() for a in rest.split(";")[0].split(",")]
         if not in_asm and (op.startswith(("scratch_", "v_accvgpr")) or any(re.match(r"a\[?\d", a) for a in args)):
             own.append(s)
-        if in_asm and op.startswith("v_mfma"):
+        mfma = op.startswith("v_mfma")
+        if in_asm and mfma:
             need = set(_regs(args[1])) | set(_regs(args[2]))
             if any(need & w for w in recent[-2:]):
                 close.append(s)
+        if not (in_asm and mfma) and not op.startswith("s_"):
+            touched = set().union(*(_regs(a.split(" ")[0]) for a in args))
+            close += ["%s; %s" % (r[2], s) for r in results if r[0] < 11 and r[1] & touched]
+        slots = int(args[0]) + 1 if op == "s_nop" else 8 if mfma else 1
+        for r in results:
+            r[0] += slots
+        results = [r for r in results if r[0] < 11]
+        if in_asm and mfma and set(_regs(args[0])):
+            results = [r for r in results if r[1] != set(_regs(args[0]))] + [[0, set(_regs(args[0])), s]]
         if op == "s_nop":
             recent += [set()] * (int(args[0]) + 1)
         else:
-            valu = op.startswith("v_") and not op.startswith(("v_mfma", "v_cmp", "v_readfirstlane", "v_readlane"))
+            valu = op.startswith("v_") and not mfma and not op.startswith(("v_cmp", "v_readfirstlane", "v_readlane"))
             recent.append(set(_regs(args[0])) if valu else set())
     return own, close
 
 
 def test_pinned_accumulator_kernels(listing):
     kernels = _kernels(listing)
-    assert len(kernels) >= 2 * len(KERNELS), [k for k, _ in kernels]
+    assert len(kernels) >= 3, [k for k, _ in kernels]  # dK/dV for both head dims, dQ for 128
     for name, lines in kernels:
         own, close = hazards(lines)
         assert sum("v_mfma" in x for x in lines) >= 32, name
@@ -86,11 +99,16 @@ def test_hazard_check_sees_planted_mistakes():
     assert hazards(ok) == ([], [])
     assert hazards([x for x in ok if "s_nop" not in x])[1]
     assert hazards(ok + ["\tv_accvgpr_read_b32 v1, a0"])[0]
+    late = ["\t;;#ASMSTART", "\tv_mfma_f32_32x32x16_bf16 v[16:31], v[8:11], a[0:3], 0", "\t;;#ASMEND"]
+    assert hazards(late + ["\ts_nop 11", "\tv_add_f32_e32 v1, v16, v2"]) == ([], [])
+    assert hazards(late + ["\ts_nop 7", "\tv_add_f32_e32 v1, v16, v2"])[1]
     assert hazards(ok + ["\tscratch_load_dword v1, off, off"])[0]
 
 
-def test_cases_choose_the_wide_kernel():
-    # the rule of use_wide() in pg_attn.hip, restated on the test sizes
-    for (p, _, s), hq, hkv, _, _ in CASES:
+def test_cases_choose_the_wide_kernels():
+    # the rules of use_wide() and use_wide_q() in pg_attn.hip, restated on the test sizes
+    for (p, _, s), hq, _, d, _ in DQ_CASES:
+        assert d == 128 and sum(p) // 8192 >= len(p) and (-(-sum(p) // 256) - (-sum(s) // 256)) * hq >= 512, (p, s)
+    for (p, _, s), hq, hkv, _, _ in CASES + DQ_CASES:
         tp, ts, ng = sum(p), sum(s), len(p)
         assert tp // 1024 >= ng and hq / hkv * (0.5 * tp + ts) / (ng * 32) * -(-tp // 256) * hkv >= 80 * 256, (p, s)
