@@ -763,12 +763,21 @@ int pg_attn_fwd_last(int dtype, int n_groups, int n_suffixes, int total_prefix, 
   a.scale_log2 = softmax_scale * pg::kLog2e;
   {
     Timed tp(PG_K_PLAN, st);
-    const RopeLayout R{L.hdr, L.ginfo, L.qoff, L.kvoff, 0};
-    if ((rc = launch_rope_plan(R, ws, n_groups, n_suffixes, total_prefix, total_suffix, cu_prefix_lens,
-                               cu_suffix_lens, group_sizes, st)))
-      return rc;
-    hipLaunchKernelGGL(pg::plan_last_kernel, dim3(1), dim3(pg::kPlanThreads), 0, st, a.hdr, a.ginfo, n_groups, L.mpw,
-                       L.nb_max, (pg::LastBlock*)(ws + L.blocks), (int*)(ws + L.nblk));
+    if (pg::plan_fits_lds(n_groups, n_suffixes) && !plan_multi()) {
+      hipLaunchKernelGGL(pg::plan_last_fused_kernel, dim3(1), dim3(pg::kPlanThreads), 0, st, cu_prefix_lens,
+                         cu_suffix_lens, group_sizes, n_groups, n_suffixes, total_prefix, total_suffix, pg::kFwdBM,
+                         pg::kKvBN, (pg::PlanHeader*)(ws + L.hdr), (pg::GroupInfoEx*)(ws + L.ginfo),
+                         (int*)(ws + L.qoff), (int*)(ws + L.kvoff), L.mpw, L.nb_max, (pg::LastBlock*)(ws + L.blocks),
+                         (int*)(ws + L.nblk));
+      if ((rc = finish_plan(a.hdr, st))) return rc;
+    } else {
+      const RopeLayout R{L.hdr, L.ginfo, L.qoff, L.kvoff, 0};
+      if ((rc = launch_rope_plan(R, ws, n_groups, n_suffixes, total_prefix, total_suffix, cu_prefix_lens,
+                                 cu_suffix_lens, group_sizes, st)))
+        return rc;
+      hipLaunchKernelGGL(pg::plan_last_kernel, dim3(1), dim3(pg::kPlanThreads), 0, st, a.hdr, a.ginfo, n_groups,
+                         L.mpw, L.nb_max, (pg::LastBlock*)(ws + L.blocks), (int*)(ws + L.nblk));
+    }
   }
   const long blocks = pg::xcd_grid_blocks((long)L.nb_max * L.nch, h_kv, 1);
   const long merge = (long)(head_dim == 128 ? pg::merge_groups<128>() : pg::merge_groups<64>()) * L.nb_max * h_kv;
