@@ -425,31 +425,14 @@ __global__ void __launch_bounds__(kPlanThreads) plan_fused_kernel(
     const int* __restrict__ cu_p, const int* __restrict__ cu_s, const int* __restrict__ gsz, int ng, int ns, int tp,
     int ts, int bm, int bkv, int kv_chunks, int split, long max_q, long max_kv, PlanHeader* hdr, GroupInfoEx* ginfo,
     int* qoff, int* kvoff, TileDesc* qtiles, int* qorder, TileDesc* kvtiles, int* kvorder, int* seg_start) {
+  // the host takes this kernel where 2 ng + ns <= kPlanThreads, so the arrays always fit
   __shared__ PlanLds lds;
   const int t = threadIdx.x;
   const GroupInfoEx* gi = lds.gi;
   const int *cs = lds.cu_s, *oq = lds.qoff, *okv = lds.kvoff;
-  bool ok;
-  int nq, nkv;
-  if (plan_fits_lds(ng, ns)) {
-    ok = plan_groups_lds(cu_p, cu_s, gsz, ng, ns, tp, ts, bm, bkv, kv_chunks, split, max_q, max_kv, hdr, ginfo, qoff,
-                         kvoff, lds);
-    nq = ok ? lds.qoff[ng] : 0;
-    nkv = ok && kvtiles ? lds.kvoff[ng] : 0;
-  } else {
-    __shared__ PlanShared sh;
-    plan_groups_body(cu_p, cu_s, gsz, ng, ns, tp, ts, bm, bkv, kv_chunks, split, max_q, max_kv, hdr, ginfo, qoff,
-                     kvoff, sh);
-    __syncthreads();
-    // the tile counts the header now holds, taken from shared memory
-    ok = !sh.err;
-    nq = ok ? sh.carry[1] : 0;
-    nkv = ok && kvtiles ? sh.carry[2] : 0;
-    gi = ginfo;
-    cs = cu_s;
-    oq = qoff;
-    okv = kvoff;
-  }
+  const bool ok = plan_groups_lds(cu_p, cu_s, gsz, ng, ns, tp, ts, bm, bkv, kv_chunks, split, max_q, max_kv, hdr,
+                                  ginfo, qoff, kvoff, lds);
+  const int nq = ok ? lds.qoff[ng] : 0, nkv = ok && kvtiles ? lds.kvoff[ng] : 0;
   // both counts are at most kPlanThreads, a host bound
   const int wq = t < nq ? plan_tile(t, cs, ng, bm, bkv, 1, split, gi, oq, qtiles, 0) : -1;
   const int wkv = t < nkv ? plan_tile(t, cs, ng, bm, bkv, kv_chunks, split, gi, okv, kvtiles, 1) : -1;

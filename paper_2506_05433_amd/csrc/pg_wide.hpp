@@ -1,5 +1,4 @@
-// Building blocks of the kernels that run one wave per SIMD with all 512 registers (pg_bwd_wide.hpp,
-// pg_fwd_wide.hpp): matrix products on pinned AGPRs, LDS copies that the compiler does not wait for.
+// Building blocks of the kernels that run one wave per SIMD with all 512 registers (pg_bwd_wide.hpp): matrix products on pinned AGPRs, LDS copies that the compiler does not wait for.
 #pragma once
 #include <type_traits>
 
