@@ -283,24 +283,6 @@ __global__ void __launch_bounds__(kWideThreads, 1) dkdv_wide_kernel(const BwdArg
         if constexpr (x == 5) copy_next();
         __builtin_amdgcn_sched_barrier(0);
       });
-      if (__builtin_expect(!full, 0)) {
-        asm volatile("");
-        const int* sg = (const int*)rv + 128;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-          const int lim = key_c[kb] - (q0_it + 4 * hh);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int4 g4 = *(const int4*)&sg[8 * i + 4 * hh];
-            const int gs[4] = {g4.x, g4.y, g4.z, g4.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const bool ok = (8 * i + e >= lim) & (key_c[kb] >= gs[e]);
-              s[kb][4 * i + e] = ok ? s[kb][4 * i + e] : -INFINITY;
-            }
-          }
-        }
-      }
     } else {
       advance();
       copy_next();
@@ -343,7 +325,30 @@ __global__ void __launch_bounds__(kWideThreads, 1) dkdv_wide_kernel(const BwdArg
         __builtin_amdgcn_sched_barrier(0);
       });
       if constexpr (KK < 8) static_for<PW + 1>([&](auto k) PG_INLINE { copy_part(decltype(k)::value, off_c); });
-      // dV^T += dO^T P; beside it dS = P (dP - Dsum), and the first operands of the next tile
+      // Boundary tile: P = 0 for pairs that do not see each other, after the exponential as in dkdv_kernel:
+      // nothing of a row (its log-sum-exp may be NaN) reaches the dV of keys it does not see.
+      if (__builtin_expect(!full, 0)) {
+        asm volatile("");
+        const int* sg = (const int*)rv + 128;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int4 g4 = *(const int4*)&sg[8 * i + 4 * hh];
+          const int gs[4] = {g4.x, g4.y, g4.z, g4.w};
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb) {
+            const int lim = key_c[kb] - (q0_it + 4 * hh) - 8 * i;
+#pragma unroll
+            for (int e = 0; e < 4; e += 2) {
+              const int r = 4 * i + e;
+              s[kb][r] = ((e >= lim) & (key_c[kb] >= gs[e])) ? s[kb][r] : 0.f;
+              s[kb][r + 1] = ((e + 1 >= lim) & (key_c[kb] >= gs[e + 1])) ? s[kb][r + 1] : 0.f;
+              pk[kb][r / 8][r % 8 / 2] = pack_bf16(s[kb][r], s[kb][r + 1]);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);  // one row block's values at a time: registers are all in use
+        }
+      }
+      // dV^T += dO^T P; beside it -dS = P (Dsum - dP), and the first operands of the next tile
       static_for<4 * DB>([&](auto x_) PG_INLINE {
         constexpr int x = decltype(x_)::value, I = x / 2, t = I / DB, db = I % DB;
         if constexpr (x % 2 == 0) {

@@ -49,3 +49,32 @@ def test_wide_backward_xours_and_repeat(which):
     b, _ = _run_both(prob)
     for n in a:
         assert torch.equal(a[n], b[n]), f"{n} differs between two runs"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_nan_query_row_leaves_dv_of_keys_it_does_not_see(d):
+    """A key's dV is a sum over the rows that see it: a row whose log-sum-exp is NaN changes no other key's. Rows
+    inside a key tile on both sides, so that the tile's mask has to keep them apart."""
+    from paper_2506_05433_amd import binding
+    lengths, hq, hkv, _, _ = CASES[0]
+    prob = make_problem("single_group", seed=720, lengths=lengths, h_q=hq, h_kv=hkv, head_dim=d)
+    dev = binding.to_device(prob, "cuda")
+    clean = binding.run_bwd(dev, binding.run_fwd(dev))
+    starts = np.concatenate([[0], np.cumsum(lengths[2])])
+    pre, suf = 1000, int(starts[6]) - 1  # the last row of member 5
+    dev["q_pre"][pre] = float("nan")
+    dev["q_suf"][suf] = float("nan")
+    got = binding.run_bwd(dev, binding.run_fwd(dev))
+    torch.cuda.synchronize()
+    dv_pre, dv_suf = got[2], got[5]
+    # every prefix key is seen by the response row, every key up to its own by a row of its own side
+    assert torch.isnan(dv_pre).all() and torch.isnan(dv_suf[int(starts[5]):suf + 1]).all()
+    others = [r for r in range(int(starts[-1])) if not int(starts[5]) <= r <= suf]
+    assert torch.equal(dv_suf[others], clean[5][others])
+    dev["q_suf"][suf] = 0.5  # now only the prefix row is NaN
+    f = binding.run_fwd(dev)
+    got = binding.run_bwd(dev, f)[2]
+    dev["q_pre"][pre] = 0.25
+    want = binding.run_bwd(dev, binding.run_fwd(dev))[2]
+    torch.cuda.synchronize()
+    assert torch.isnan(got[:pre + 1]).all() and torch.equal(got[pre + 1:], want[pre + 1:])
