@@ -456,7 +456,8 @@ def cpu_model():
     return None
 
 
-ATTN_SOURCES = ("pg_attn.hip", "pg_bwd.hpp", "pg_bwd_wide.hpp", "pg_common.hpp", "pg_fwd.hpp", "pg_plan.hpp", "pg_types.hpp", "pg_wide.hpp")
+ATTN_SOURCES = ("pg_attn.hip", "pg_bwd.hpp", "pg_bwd_wide.hpp", "pg_common.hpp", "pg_fwd.hpp", "pg_layout.hpp", "pg_plan.hpp",
+                "pg_types.hpp", "pg_wide.hpp")
 
 
 def kernel_source_sha():

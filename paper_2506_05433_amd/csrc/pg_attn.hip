@@ -16,6 +16,7 @@
 #include "pg_bwd.hpp"
 #include "pg_bwd_wide.hpp"
 #include "pg_fwd.hpp"
+#include "pg_layout.hpp"
 #include "pg_plan.hpp"
 #include "pg_last.hpp"
 #include "pg_rope.hpp"
@@ -27,6 +28,10 @@
 __device__ __align__(256) char scratch[PG_NOALLOC_SCRATCH_BYTES];
 
 namespace {
+
+using pg::align_up;
+using pg::ceil_div_l;
+using pg::Layout;
 
 thread_local std::string g_last_error;
 
@@ -40,100 +45,6 @@ int fail(int status, const char* fmt, ...) {
   g_last_error = buf;
   return status;
 }
-
-constexpr size_t kAlign = 256;
-size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
-
-long ceil_div_l(long a, long b) { return (a + b - 1) / b; }
-
-// Workspace layout shared by the forward and backward calls.
-struct Layout {
-  size_t hdr, ginfo, qoff, kvoff, qtiles, qorder, kvtiles, kvorder, seg, dsum, lse2, part, xrow, total;
-  long max_q, max_kv;
-  int kv_chunks, split;
-  int bkv;  // keys per key tile: kKvBN, or kWideBN for dkdv_wide_kernel
-  int bm;   // query rows per query tile: kFwdBM, or kWideBM for the 256-row kernels
-};
-
-// Pieces each prefix key tile's query walk is split into for the dK/dV kernel: enough
-// workgroups to balance the long prefix walks over the CUs (about 512 prefix pieces, i.e.
-// two per CU), at most 8, and 1 when there are already that many prefix key tiles. More
-// pieces balance better but each adds a full fp32 partial to write and reduce; measured on
-// the single-group and large-group workloads, 512 beats 256 and 1024-4096. A piece keeps at
-// least 16 64-row query tiles of the average walk (a group's rows, once per query head of
-// the kv head): shorter pieces cost more in their fixed start-up and in the reduce launch
-// than they save. A grid of at most 128 key tiles (half the CUs) runs as long as its
-// longest walk whatever the total work, so there pieces of one such tile pay off. With 256-key
-// tiles (one workgroup per CU) about 384 pieces are best, and two up to 768: one group of P 4096,
-// 32/8 heads (136 tiles) takes 913, 909, 1050, 982 us with 2, 3, 4, 6 pieces, P 16384 (520 tiles)
-// 6.30 ms with one and 6.17 with two.
-int kv_chunks_for(int ng, int tp, int ts, int h_q, int h_kv, int bkv) {
-  if (tp <= 0 || h_kv <= 0) return 1;
-  const long tiles = (ceil_div_l(tp, bkv) + ng) * (long)h_kv;
-  long c = ceil_div_l(512, tiles);
-  if (bkv == pg::kWideBN) c = tiles >= 768 ? 1 : std::max(2L, ceil_div_l(384, tiles));
-  const long walk = ceil_div_l((long)tp + ts, (long)(ng > 0 ? ng : 1) * 64) * (h_q / h_kv);
-  const long min_piece = 2 * tiles <= 256 ? 1 : 16;
-  if (c > walk / min_piece) c = walk / min_piece;
-  return (int)(c < 1 ? 1 : (c > 8 ? 8 : c));
-}
-
-// Problems whose stacked query tiles x heads cannot fill the 256 CUs tile each member's
-// responses on their own (see response_tiles in the planner): their time is the longest
-// tile walk, not the total work.
-constexpr long kSplitBelow = 256;
-
-// Whether the backward runs dkdv_wide_kernel (256-key tiles). It does the same work in fewer, longer
-// workgroups, so it needs enough of it: at least 80 tile steps (32 query rows x 256 keys) per CU in the
-// prefix walks, and prefixes long enough that a tile's 256 keys are rarely ragged. Measured (dK/dV
-// plus reduction, dkdv_kernel -> wide): 24 steps per CU 112 -> 123 us, 55 steps 194 -> 203 us, 112 steps
-// 335 -> 297 us, 232 steps 718 -> 675 us; 184 steps but prefixes of 300 rows 540 -> 608 us.
-bool use_wide(int dtype, int ng, int tp, int ts, int h_q, int h_kv) {
-  if (dtype != PG_BF16 || ng <= 0 || h_kv <= 0 || tp / 1024 < ng) return false;
-  const double walk = (double)(h_q / h_kv) * (0.5 * tp + ts) / ((double)ng * pg::kWideBQ);
-  return walk * (double)ceil_div_l(tp, pg::kWideBN) * h_kv >= 80.0 * 256.0;
-}
-
-// Whether the backward runs dq_wide_kernel (256-row query tiles). Its workgroups have a CU to themselves,
-// so loading their rows and storing dQ is not hidden: it needs long key walks, and enough tiles to give
-// every CU two. Measured (dq_kernel -> wide), one group of 16/4 or 32/8 heads: P 1024 1278 -> 1468 us, 4096
-// 2477 -> 2500 us, 8192 804 -> 770 us, 16384 4664 -> 4420 us. With 64-wide heads the vector work per
-// product doubles and one wave per SIMD cannot issue it (206 -> 278 us on prefixes of 179..2530).
-bool use_wide_q(int dtype, int ng, int tp, int ts, int h_q, int d) {
-  return dtype == PG_BF16 && d == 128 && ng > 0 && tp / 8192 >= ng &&
-         (ceil_div_l(tp, pg::kWideBM) + ceil_div_l(ts, pg::kWideBM)) * h_q >= 512;
-}
-
-Layout make_layout(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d, bool bwd, bool wide = false,
-                   bool wide_q = false) {
-  Layout L{};
-  L.bm = wide_q ? pg::kWideBM : pg::kFwdBM;
-  L.bkv = wide ? pg::kWideBN : pg::kKvBN;
-  L.kv_chunks = bwd ? kv_chunks_for(ng, tp, ts, h_q, h_kv, L.bkv) : 1;
-  L.split = !wide_q && (ceil_div_l(tp, pg::kFwdBM) + ceil_div_l(ts, pg::kFwdBM) + ng) * (long)h_q < kSplitBelow ? 1 : 0;
-  // bounds of the tile lists in either tiling (splitting adds at most one tile per member)
-  L.max_q = ceil_div_l(tp, L.bm) + ceil_div_l(ts, L.bm) + 2L * ng + ns;
-  L.max_kv = bwd ? (ceil_div_l(tp, L.bkv) + ng) * L.kv_chunks + ceil_div_l(ts, L.bkv) + ng + ns : 0;
-  size_t off = 0;
-  auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
-  const size_t rows = (size_t)tp + (size_t)ts;  // sizes are non-negative ints: no overflow in 64 bits
-  L.hdr = take(sizeof(pg::PlanHeader));
-  L.ginfo = take(sizeof(pg::GroupInfoEx) * (size_t)(ng > 0 ? ng : 1));
-  L.qoff = take(sizeof(int) * ((size_t)ng + 1));
-  L.kvoff = take(sizeof(int) * ((size_t)ng + 1));
-  L.qtiles = take(sizeof(pg::TileDesc) * (size_t)(L.max_q > 0 ? L.max_q : 1));
-  L.qorder = take(sizeof(int) * (size_t)(L.max_q > 0 ? L.max_q : 1));
-  L.kvtiles = take(sizeof(pg::TileDesc) * (size_t)(L.max_kv > 0 ? L.max_kv : 1));
-  L.kvorder = take(sizeof(int) * (size_t)(L.max_kv > 0 ? L.max_kv : 1));
-  L.seg = take(sizeof(int) * (size_t)(ts > 0 ? ts : 1));
-  L.dsum = bwd ? take(sizeof(float) * (size_t)h_q * (rows > 0 ? rows : 1)) : off;
-  L.lse2 = bwd && wide ? take(sizeof(float) * (size_t)h_q * (rows > 0 ? rows : 1)) : off;
-  L.part = (bwd && L.kv_chunks > 1) ? take(sizeof(float) * (size_t)L.kv_chunks * 2 * (size_t)tp * h_kv * d) : off;
-  L.xrow = bwd ? take(sizeof(int) * (rows > 0 ? rows : 1)) : off;
-  L.total = off;
-  return L;
-}
-
 
 // ---------------------------------------------------------------- kernel timing
 // Optional HIP-event brackets around each launch, recorded on the launch's own
@@ -281,7 +192,7 @@ int launch_plan(const Common& c, const Layout& L, char* ws, const int32_t* cu_p,
   int* qo = (int*)(ws + L.qorder);
   // the one-block planner also fills the per-row member starts when there are few rows (one
   // launch less; over many rows one block is slower than the wide kernel)
-  const bool one_block = L.max_q <= pg::kPlanThreads && (!bwd || L.max_kv <= pg::kPlanThreads) && !plan_multi();
+  const bool one_block = pg::one_block_plan(L, bwd) && !plan_multi();
   const bool fused_seg = one_block && c.ts <= kFusedSegRows;
   if (one_block) {
     // every tile list fits one block: groups, tiles and ranks in one launch
@@ -340,23 +251,23 @@ void launch_fwd(const pg::FwdArgs& a, long max_q, hipStream_t st) {
 }
 
 template <typename T, int D>
-void launch_bwd(const pg::BwdArgs& a, long max_q, long max_kv, int bm, bool wide, hipStream_t st) {
+void launch_bwd(const pg::BwdArgs& a, const Layout& L, hipStream_t st) {
   // dQ first: it also writes Dsum, which the dK/dV kernel reads
-  if (max_q > 0) {
+  if (L.max_q > 0) {
     Timed tm(PG_K_DQ, st);
-    const long blocks = pg::xcd_grid_blocks(max_q, a.h_q, a.h_q / a.h_kv);
-    if (bm == pg::kWideBM) {
+    const long blocks = pg::xcd_grid_blocks(L.max_q, a.h_q, a.h_q / a.h_kv);
+    if (L.bm == pg::kWideBM) {
       if constexpr (sizeof(T) == 2 && D == 128)
         hipLaunchKernelGGL((pg::dq_wide_kernel<D>), dim3((unsigned)blocks), dim3(pg::kWideThreads), 0, st, a);
     } else {
       hipLaunchKernelGGL((pg::dq_kernel<T, D>), dim3((unsigned)blocks), dim3(pg::kDqThreads), 0, st, a);
     }
   }
-  if (max_kv > 0) {
+  if (L.max_kv > 0) {
     {
       Timed tm(PG_K_DKDV, st);
-      const long blocks = pg::xcd_grid_blocks(max_kv, a.h_kv, 1);
-      if (wide) {
+      const long blocks = pg::xcd_grid_blocks(L.max_kv, a.h_kv, 1);
+      if (L.bkv == pg::kWideBN) {
         if constexpr (sizeof(T) == 2)
           hipLaunchKernelGGL((pg::dkdv_wide_kernel<D>), dim3((unsigned)blocks), dim3(pg::kWideThreads), 0, st, a);
       } else {
@@ -379,7 +290,7 @@ int fwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
              const void* k_pre, const void* v_pre, const void* q_suf, const void* k_suf, const void* v_suf,
              void* o_pre, void* o_suf, float* lse_pre, float* lse_suf, bool xl, void* workspace,
              size_t workspace_bytes, void* stream) {
-  const Layout L = make_layout(c.ng, c.ns, c.tp, c.ts, c.h_q, c.h_kv, c.d, false);
+  const Layout L = pg::make_layout(c.ng, c.ns, c.tp, c.ts, c.h_q, c.h_kv, c.d, false);
   if (!workspace || workspace_bytes < L.total)
     return fail(PG_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace_bytes, L.total);
   int rc = device_ready();
@@ -413,9 +324,7 @@ int fwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
 // out: dq_pre, dk_pre, dv_pre, dq_suf, dk_suf, dv_suf.
 int bwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const int32_t* gsz, const void* const* in,
              void* const* out, bool xl, void* workspace, size_t workspace_bytes, void* stream) {
-  const bool wide = use_wide(c.dtype, c.ng, c.tp, c.ts, c.h_q, c.h_kv);
-  const Layout L = make_layout(c.ng, c.ns, c.tp, c.ts, c.h_q, c.h_kv, c.d, true, wide,
-                               use_wide_q(c.dtype, c.ng, c.tp, c.ts, c.h_q, c.d));
+  const Layout L = pg::bwd_layout(c.dtype, c.ng, c.ns, c.tp, c.ts, c.h_q, c.h_kv, c.d);
   if (!workspace || workspace_bytes < L.total)
     return fail(PG_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace_bytes, L.total);
   int rc = device_ready();
@@ -430,7 +339,7 @@ int bwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
   a.do_pre = in[10]; a.do_suf = in[11];
   a.dq_pre = out[0]; a.dk_pre = out[1]; a.dv_pre = out[2]; a.dq_suf = out[3]; a.dk_suf = out[4]; a.dv_suf = out[5];
   a.dsum = (float*)(ws + L.dsum);
-  a.lse2 = wide ? (float*)(ws + L.lse2) : nullptr;
+  a.lse2 = L.bkv == pg::kWideBN ? (float*)(ws + L.lse2) : nullptr;
   a.part = (float*)(ws + L.part);
   a.kv_chunks = L.kv_chunks;
   a.hdr = (const pg::PlanHeader*)(ws + L.hdr);
@@ -446,11 +355,11 @@ int bwd_impl(const Common& c, const int32_t* cu_p, const int32_t* cu_s, const in
   a.xl = xl ? 1 : 0;
   a.xrow = (const int*)(ws + L.xrow);
   if (c.dtype == PG_BF16) {
-    if (c.d == 128) launch_bwd<pg::bf16, 128>(a, L.max_q, L.max_kv, L.bm, wide, st);
-    else launch_bwd<pg::bf16, 64>(a, L.max_q, L.max_kv, L.bm, wide, st);
+    if (c.d == 128) launch_bwd<pg::bf16, 128>(a, L, st);
+    else launch_bwd<pg::bf16, 64>(a, L, st);
   } else {
-    if (c.d == 128) launch_bwd<float, 128>(a, L.max_q, L.max_kv, L.bm, wide, st);
-    else launch_bwd<float, 64>(a, L.max_q, L.max_kv, L.bm, wide, st);
+    if (c.d == 128) launch_bwd<float, 128>(a, L, st);
+    else launch_bwd<float, 64>(a, L, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "backward launch");
@@ -537,7 +446,7 @@ size_t pg_attn_fwd_workspace_size(int n_groups, int n_suffixes, int total_prefix
   if (n_groups < 0 || n_suffixes < 0 || total_prefix < 0 || total_suffix < 0 || h_q < 0 || h_kv < 0 ||
       head_dim < 0)
     return 0;
-  return make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, false).total;
+  return pg::make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, false).total;
 }
 
 size_t pg_attn_bwd_workspace_size(int n_groups, int n_suffixes, int total_prefix, int total_suffix, int h_q,
@@ -545,8 +454,7 @@ size_t pg_attn_bwd_workspace_size(int n_groups, int n_suffixes, int total_prefix
   if (n_groups < 0 || n_suffixes < 0 || total_prefix < 0 || total_suffix < 0 || h_q < 0 || h_kv < 0 ||
       head_dim < 0)
     return 0;
-  return std::max(make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, true).total,
-                  make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, true, true).total);
+  return pg::bwd_workspace(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim);
 }
 
 const char* pg_status_string(int s) {
@@ -614,7 +522,7 @@ int pg_attn_fwd_noalloc(int dtype, int n_groups, int n_suffixes, int total_prefi
     return fail(PG_EINVAL, "a prefix tensor pointer is NULL");
   if (total_suffix > 0 && (!q_suf || !k_suf || !v_suf || !o_suf || !lse_suf))
     return fail(PG_EINVAL, "a suffix tensor pointer is NULL");
-  const size_t need = make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, false).total;
+  const size_t need = pg::make_layout(n_groups, n_suffixes, total_prefix, total_suffix, h_q, h_kv, head_dim, false).total;
   if (need > (size_t)PG_NOALLOC_SCRATCH_BYTES)
     return fail(PG_EUNSUPPORTED, "the plan needs %zu bytes of scratch, more than the %u held for pg_attn_fwd_noalloc",
                 need, (unsigned)PG_NOALLOC_SCRATCH_BYTES);

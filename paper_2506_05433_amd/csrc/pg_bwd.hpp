@@ -55,8 +55,7 @@ struct BwdArgs {
 // exp/VALU work overlaps the other's matrix instructions. Query tiles are
 // triple-buffered in LDS (P-waves read tile i, G-waves tile i-1; the G-waves load tile
 // i+1 through registers and write it to LDS after their work on tile i-1).
-constexpr int kKvGroups = 4;                 // 32-key groups per workgroup
-constexpr int kKvBN = 32 * kKvGroups;        // keys per workgroup
+constexpr int kKvGroups = kKvBN / 32;        // 32-key groups per workgroup
 constexpr int kKvThreads = 128 * kKvGroups;  // a P-wave and a G-wave per key group
 
 template <typename T>
@@ -391,7 +390,6 @@ __global__ void __launch_bounds__(256) kv_reduce_kernel(const BwdArgs a) {
 }
 
 // ------------------------------------------------------------------ dQ (query-stationary)
-constexpr int kDqBM = 128;
 constexpr int kDqBN = 64;
 constexpr int kDqThreads = 256;
 

@@ -26,9 +26,7 @@
 
 namespace pg {
 
-constexpr int kWideKeys = 64;                    // keys per wave
-constexpr int kWideBN = 4 * kWideKeys;           // keys per workgroup
-constexpr int kWideBQ = 32;                      // query rows per staged tile
+constexpr int kWideKeys = kWideBN / 4;  // keys per wave
 
 constexpr int kDenseRow = 1 << 30;  // stands for a row that sees every key
 

@@ -38,7 +38,6 @@ struct FwdArgs {
   int xl;
 };
 
-constexpr int kFwdBM = 128;  // query rows per workgroup
 constexpr int kFwdBN = 64;   // keys per tile
 constexpr int kFwdThreads = 256;
 

@@ -1,0 +1,123 @@
+// Host-side choices that depend on a call's sizes alone: which kernels it runs (their tile sizes), into how
+// many pieces prefix walks are cut, and where each array of the plan lies in the workspace. Plain C++: the
+// tests compile it for the host and read these choices from it.
+#pragma once
+#include <stddef.h>
+
+#include <algorithm>
+
+#include "../../include/pg_attn.h"
+#include "pg_plan.hpp"
+
+namespace pg {
+
+constexpr size_t kAlign = 256;
+inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+
+inline long ceil_div_l(long a, long b) { return (a + b - 1) / b; }
+
+// Workspace layout shared by the forward and backward calls.
+struct Layout {
+  size_t hdr, ginfo, qoff, kvoff, qtiles, qorder, kvtiles, kvorder, seg, dsum, lse2, part, xrow, total;
+  long max_q, max_kv;
+  int kv_chunks, split;
+  int bkv;  // keys per key tile: kKvBN, or kWideBN for dkdv_wide_kernel
+  int bm;   // query rows per query tile: kFwdBM, or kWideBM for the 256-row kernels
+};
+
+// Pieces each prefix key tile's query walk is split into for the dK/dV kernel: enough
+// workgroups to balance the long prefix walks over the CUs (about 512 prefix pieces, i.e.
+// two per CU), at most 8, and 1 when there are already that many prefix key tiles. More
+// pieces balance better but each adds a full fp32 partial to write and reduce; measured on
+// the single-group and large-group workloads, 512 beats 256 and 1024-4096. A piece keeps at
+// least 16 64-row query tiles of the average walk (a group's rows, once per query head of
+// the kv head): shorter pieces cost more in their fixed start-up and in the reduce launch
+// than they save. A grid of at most 128 key tiles (half the CUs) runs as long as its
+// longest walk whatever the total work, so there pieces of one such tile pay off. With 256-key
+// tiles (one workgroup per CU) about 384 pieces are best, and two up to 768: one group of P 4096,
+// 32/8 heads (136 tiles) takes 913, 909, 1050, 982 us with 2, 3, 4, 6 pieces, P 16384 (520 tiles)
+// 6.30 ms with one and 6.17 with two.
+inline int kv_chunks_for(int ng, int tp, int ts, int h_q, int h_kv, int bkv) {
+  if (tp <= 0 || h_kv <= 0) return 1;
+  const long tiles = (ceil_div_l(tp, bkv) + ng) * (long)h_kv;
+  long c = ceil_div_l(512, tiles);
+  if (bkv == kWideBN) c = tiles >= 768 ? 1 : std::max(2L, ceil_div_l(384, tiles));
+  const long walk = ceil_div_l((long)tp + ts, (long)(ng > 0 ? ng : 1) * 64) * (h_q / h_kv);
+  const long min_piece = 2 * tiles <= 256 ? 1 : 16;
+  if (c > walk / min_piece) c = walk / min_piece;
+  return (int)(c < 1 ? 1 : (c > 8 ? 8 : c));
+}
+
+// Problems whose stacked query tiles x heads cannot fill the 256 CUs tile each member's
+// responses on their own (see response_tiles in the planner): their time is the longest
+// tile walk, not the total work.
+constexpr long kSplitBelow = 256;
+
+// Whether the backward runs dkdv_wide_kernel (256-key tiles). It does the same work in fewer, longer
+// workgroups, so it needs enough of it: at least 80 tile steps (32 query rows x 256 keys) per CU in the
+// prefix walks, and prefixes long enough that a tile's 256 keys are rarely ragged. Measured (dK/dV
+// plus reduction, dkdv_kernel -> wide): 24 steps per CU 112 -> 123 us, 55 steps 194 -> 203 us, 112 steps
+// 335 -> 297 us, 232 steps 718 -> 675 us; 184 steps but prefixes of 300 rows 540 -> 608 us.
+inline bool use_wide(int dtype, int ng, int tp, int ts, int h_q, int h_kv) {
+  if (dtype != PG_BF16 || ng <= 0 || h_kv <= 0 || tp / 1024 < ng) return false;
+  const double walk = (double)(h_q / h_kv) * (0.5 * tp + ts) / ((double)ng * kWideBQ);
+  return walk * (double)ceil_div_l(tp, kWideBN) * h_kv >= 80.0 * 256.0;
+}
+
+// Whether the backward runs dq_wide_kernel (256-row query tiles). Its workgroups have a CU to themselves,
+// so loading their rows and storing dQ is not hidden: it needs long key walks, and enough tiles to give
+// every CU two. Measured (dq_kernel -> wide), one group of 16/4 or 32/8 heads: P 1024 1278 -> 1468 us, 4096
+// 2477 -> 2500 us, 8192 804 -> 770 us, 16384 4664 -> 4420 us. With 64-wide heads the vector work per
+// product doubles and one wave per SIMD cannot issue it (206 -> 278 us on prefixes of 179..2530).
+inline bool use_wide_q(int dtype, int ng, int tp, int ts, int h_q, int d) {
+  return dtype == PG_BF16 && d == 128 && ng > 0 && tp / 8192 >= ng &&
+         (ceil_div_l(tp, kWideBM) + ceil_div_l(ts, kWideBM)) * h_q >= 512;
+}
+
+inline Layout make_layout(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d, bool bwd, bool wide = false,
+                          bool wide_q = false) {
+  Layout L{};
+  L.bm = wide_q ? kWideBM : kFwdBM;
+  L.bkv = wide ? kWideBN : kKvBN;
+  L.kv_chunks = bwd ? kv_chunks_for(ng, tp, ts, h_q, h_kv, L.bkv) : 1;
+  L.split = !wide_q && (ceil_div_l(tp, kFwdBM) + ceil_div_l(ts, kFwdBM) + ng) * (long)h_q < kSplitBelow ? 1 : 0;
+  // bounds of the tile lists in either tiling (splitting adds at most one tile per member)
+  L.max_q = ceil_div_l(tp, L.bm) + ceil_div_l(ts, L.bm) + 2L * ng + ns;
+  L.max_kv = bwd ? (ceil_div_l(tp, L.bkv) + ng) * L.kv_chunks + ceil_div_l(ts, L.bkv) + ng + ns : 0;
+  size_t off = 0;
+  auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
+  const size_t rows = (size_t)tp + (size_t)ts;  // sizes are non-negative ints: no overflow in 64 bits
+  L.hdr = take(sizeof(PlanHeader));
+  L.ginfo = take(sizeof(GroupInfoEx) * (size_t)(ng > 0 ? ng : 1));
+  L.qoff = take(sizeof(int) * ((size_t)ng + 1));
+  L.kvoff = take(sizeof(int) * ((size_t)ng + 1));
+  L.qtiles = take(sizeof(TileDesc) * (size_t)(L.max_q > 0 ? L.max_q : 1));
+  L.qorder = take(sizeof(int) * (size_t)(L.max_q > 0 ? L.max_q : 1));
+  L.kvtiles = take(sizeof(TileDesc) * (size_t)(L.max_kv > 0 ? L.max_kv : 1));
+  L.kvorder = take(sizeof(int) * (size_t)(L.max_kv > 0 ? L.max_kv : 1));
+  L.seg = take(sizeof(int) * (size_t)(ts > 0 ? ts : 1));
+  L.dsum = bwd ? take(sizeof(float) * (size_t)h_q * (rows > 0 ? rows : 1)) : off;
+  L.lse2 = bwd && wide ? take(sizeof(float) * (size_t)h_q * (rows > 0 ? rows : 1)) : off;
+  L.part = (bwd && L.kv_chunks > 1) ? take(sizeof(float) * (size_t)L.kv_chunks * 2 * (size_t)tp * h_kv * d) : off;
+  L.xrow = bwd ? take(sizeof(int) * (rows > 0 ? rows : 1)) : off;
+  L.total = off;
+  return L;
+}
+
+// The layout pg_attn_bwd and pg_attn_bwd_xours use.
+inline Layout bwd_layout(int dtype, int ng, int ns, int tp, int ts, int h_q, int h_kv, int d) {
+  return make_layout(ng, ns, tp, ts, h_q, h_kv, d, true, use_wide(dtype, ng, tp, ts, h_q, h_kv),
+                     use_wide_q(dtype, ng, tp, ts, h_q, d));
+}
+
+inline size_t bwd_workspace(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d) {
+  return std::max(make_layout(ng, ns, tp, ts, h_q, h_kv, d, true).total,
+                  make_layout(ng, ns, tp, ts, h_q, h_kv, d, true, true).total);
+}
+
+// Whether plan_fused_kernel plans the call: every tile list fits its one block.
+inline bool one_block_plan(const Layout& L, bool bwd) {
+  return L.max_q <= kPlanThreads && (!bwd || L.max_kv <= kPlanThreads);
+}
+
+}  // namespace pg

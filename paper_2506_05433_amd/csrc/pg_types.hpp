@@ -6,6 +6,13 @@
 
 namespace pg {
 
+// Tile sizes of the attention kernels.
+constexpr int kFwdBM = 128;   // query rows per workgroup: fwd_kernel, dq_kernel
+constexpr int kKvBN = 128;    // keys per workgroup: dkdv_kernel
+constexpr int kWideBM = 256;  // query rows per workgroup: dq_wide_kernel
+constexpr int kWideBN = 256;  // keys per workgroup: dkdv_wide_kernel
+constexpr int kWideBQ = 32;   // query rows per staged tile: dkdv_wide_kernel
+
 // Tile descriptor produced by the planner.
 //  q tiles : kind 0 = prefix query rows [row0,row1) of group `group` (packed prefix index);
 //            kind 1 = response query rows [row0,row1) (packed suffix index), which may span

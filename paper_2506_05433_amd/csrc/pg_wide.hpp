@@ -153,7 +153,6 @@ __device__ __forceinline__ V pick(bool cond, V a, V b) { return cond ? a : b; }
 
 template <int N>
 using Int = std::integral_constant<int, N>;
-constexpr int kWideBM = 256;  // query rows per workgroup, 64 per wave
 constexpr int kWideBK = 32;   // keys per staged tile
 
 // Copies of 32-row K and V tiles into a ring of LDS stages, shared by the query-stationary kernels:

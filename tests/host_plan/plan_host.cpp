@@ -5,22 +5,39 @@
 //
 // stdin: mode (0 = one-block planner, 1 = multi-kernel planner), ng, ns, tp, ts, bm, bkv,
 //        kv_chunks, split, max_q, max_kv, then cu_prefix_lens[ng+1], cu_suffix_lens[ns+1],
-//        group_sizes[ng].
+//        group_sizes[ng]; or mode 2 (the library's choices for a backward of these sizes) and
+//        lines of dtype, ng, ns, tp, ts, h_q, h_kv, d, wide, wide_q, the last two 0 or 1 for a
+//        given tiling or -1 for the library's rule.
 // stdout: error n_qtiles n_kvtiles, then one line per query tile in rank order
 //         ("q kind group row0 row1 aux work chunk nchunks"), the same for kv tiles ("k ..."),
-//         then "s" followed by the per-row member starts (when the plan is valid).
+//         then "s" followed by the per-row member starts (when the plan is valid); in mode 2, per
+//         line: bm bkv kv_chunks split max_q max_kv one_block workspace size_query.
 #include <cstdio>
 #include <memory>
 
+#include "pg_layout.hpp"
 #include "pg_plan.hpp"
 
 using namespace pg;
 
+static int print_layouts() {
+  int dtype, ng, ns, tp, ts, hq, hkv, d, wide, wide_q;
+  while (scanf("%d %d %d %d %d %d %d %d %d %d", &dtype, &ng, &ns, &tp, &ts, &hq, &hkv, &d, &wide, &wide_q) == 10) {
+    const Layout L = wide < 0 ? bwd_layout(dtype, ng, ns, tp, ts, hq, hkv, d)
+                              : make_layout(ng, ns, tp, ts, hq, hkv, d, true, wide != 0, wide_q != 0);
+    printf("%d %d %d %d %ld %ld %d %zu %zu\n", L.bm, L.bkv, L.kv_chunks, L.split, L.max_q, L.max_kv,
+           (int)one_block_plan(L, true), L.total, bwd_workspace(ng, ns, tp, ts, hq, hkv, d));
+  }
+  return 0;
+}
+
 int main() {
   int mode, ng, ns, tp, ts, bm, bkv, kvc, split;
   long max_q, max_kv;
-  if (scanf("%d %d %d %d %d %d %d %d %d %ld %ld", &mode, &ng, &ns, &tp, &ts, &bm, &bkv, &kvc, &split, &max_q,
-            &max_kv) != 11)
+  if (scanf("%d", &mode) != 1) return 2;
+  if (mode == 2) return print_layouts();
+  if (scanf("%d %d %d %d %d %d %d %d %ld %ld", &ng, &ns, &tp, &ts, &bm, &bkv, &kvc, &split, &max_q,
+            &max_kv) != 10)
     return 2;
   std::unique_ptr<int[]> cu_p(new int[ng + 1]), cu_s(new int[ns + 1]), gsz(new int[ng > 0 ? ng : 1]);
   for (int i = 0; i <= ng; ++i) if (scanf("%d", &cu_p[i]) != 1) return 2;

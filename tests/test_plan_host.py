@@ -2,8 +2,8 @@
 
 * Inconsistent grouping arrays, including group sizes whose 32-bit sum wraps around to
   n_suffixes, are flagged and never make the planner read past an array.
-* Valid arrays: the one-block and the multi-kernel planners give the same plan, and the
-  plan is the tiling the kernels assume (prefix tiles of every group, response rows of
+* Valid arrays: the one-block and the multi-kernel planners give the same plan for every
+  tiling the library runs, and the plan is what the kernels assume (prefix tiles of every group, response rows of
   every group stacked into tiles, per-tile member bounds, longest-first order).
 * Every load the attention kernels derive from the plan (key/value tiles of the forward
   and dQ kernels, query tiles of the dK/dV walks, per-row tables) stays inside its tensor
@@ -22,13 +22,13 @@ from paper_2506_05433_amd.inputs import WORKLOADS, Workload, draw_lengths
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HERE = os.path.join(ROOT, "tests", "host_plan")
 CSRC = os.path.join(ROOT, "paper_2506_05433_amd", "csrc")
-BM, BKV = 128, 128           # query rows per forward/dQ tile, keys per dK/dV workgroup
-BN = 64                      # keys per forward/dQ key tile
-BQ = {"bf16": 64, "fp32": 32}  # query rows per dK/dV query tile
+BN = {128: 64, 256: 32}  # keys per staged tile, by the query rows of a workgroup
+BQ = {"bf16": 64, "fp32": 32}  # query rows per staged tile of the 128-key dK/dV kernel; 32 for 256 keys
+DTYPES = {"bf16": 0, "fp32": 1}
+TILINGS = [(0, 0), (1, 0), (1, 1)]  # 128 rows and keys, 128 rows and 256 keys, 256 rows and keys
 
 
-@pytest.fixture(scope="module")
-def planner(tmp_path_factory):
+def build_planner(tmp_path_factory):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("g++ not available")
@@ -41,32 +41,31 @@ def planner(tmp_path_factory):
     return exe
 
 
-def kv_chunks_for(ng, tp, ts, h_q, h_kv):
-    """The library's split of long prefix key walks (pg_attn.hip, kv_chunks_for)."""
-    if tp <= 0 or h_kv <= 0:
-        return 1
-    tiles = (math.ceil(tp / BKV) + ng) * h_kv
-    c = math.ceil(512 / tiles)
-    walk = math.ceil((tp + ts) / (max(ng, 1) * 64)) * (h_q // h_kv)
-    c = min(c, walk // (1 if 2 * tiles <= 256 else 16))
-    return max(1, min(8, c))
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    return build_planner(tmp_path_factory)
 
 
-def split_for(ng, tp, ts, h_q):
-    """The library's choice of member-aligned response tiles (pg_attn.hip, make_layout)."""
-    return int((math.ceil(tp / BM) + math.ceil(ts / BM) + ng) * h_q < 256)
+def layouts(exe, calls):
+    """The library's choices (pg_layout.hpp) for backward calls (dtype, ng, ns, tp, ts, h_q, h_kv, d) or, with two
+    more values, for a given tiling (wide, wide_q)."""
+    keys = ("bm", "bkv", "kvc", "split", "max_q", "max_kv", "one_block", "workspace", "size_query")
+    text = "2\n" + "\n".join(" ".join(str(int(x)) for x in (tuple(c) + (-1, -1))[:10]) for c in calls)
+    res = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0, res.stderr[-4000:]
+    return [dict(zip(keys, map(int, line.split()))) for line in res.stdout.strip().split("\n")]
 
 
-def bounds(ng, ns, tp, ts, kvc):
-    return (math.ceil(tp / BM) + math.ceil(ts / BM) + 2 * ng + ns,
-            (math.ceil(tp / BKV) + ng) * kvc + math.ceil(ts / BKV) + ng + ns)
+def bounds(ng, ns, tp, ts, kvc, bm, bkv):
+    return (math.ceil(tp / bm) + math.ceil(ts / bm) + 2 * ng + ns,
+            (math.ceil(tp / bkv) + ng) * kvc + math.ceil(ts / bkv) + ng + ns)
 
 
-def run_plan(exe, cu_p, cu_s, gsz, ng, ns, tp, ts, mode=0, kvc=1, split=0, max_q=None, max_kv=None):
-    bq, bkv = bounds(ng, ns, tp, ts, kvc)
+def run_plan(exe, cu_p, cu_s, gsz, ng, ns, tp, ts, mode=0, kvc=1, split=0, max_q=None, max_kv=None, bm=128, bkv=128):
+    bq, bk = bounds(ng, ns, tp, ts, kvc, bm, bkv)
     max_q = bq if max_q is None else max_q
-    max_kv = bkv if max_kv is None else max_kv
-    text = " ".join(str(int(x)) for x in [mode, ng, ns, tp, ts, BM, BKV, kvc, split, max_q, max_kv, *cu_p, *cu_s,
+    max_kv = bk if max_kv is None else max_kv
+    text = " ".join(str(int(x)) for x in [mode, ng, ns, tp, ts, bm, bkv, kvc, split, max_q, max_kv, *cu_p, *cu_s,
                                            *gsz])
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0", UBSAN_OPTIONS="halt_on_error=1")
     res = subprocess.run([exe], input=text, capture_output=True, text=True, env=env, timeout=300)
@@ -126,7 +125,7 @@ def test_inconsistent_offsets_are_flagged(planner, bad):
         assert err == 1 and not q and not k
 
 
-def expected_tiles(prefix, groups, suffix, kvc, split=0):
+def expected_tiles(prefix, groups, suffix, kvc, split=0, bm=128, bkv=128):
     """The tiling the kernels assume, as sets of (kind, group, row0, row1, aux, chunk, nchunks): prefix tiles
     of every group; response rows of a group stacked into tiles across member boundaries, or with ``split``
     each member's rows tiled on their own."""
@@ -138,28 +137,28 @@ def expected_tiles(prefix, groups, suffix, kvc, split=0):
         spans = ([(int(cu_s[i]), int(cu_s[i + 1])) for i in range(m, m + gs)] if split
                  else [(int(cu_s[m]), int(cu_s[m + gs]))])
         owner = lambda row: int(np.searchsorted(cu_s, row, side="right") - 1)  # noqa: E731
-        for r0 in range(p0, p1, BM):
-            q.add((0, g, r0, min(r0 + BM, p1), 0, 0, 1))
-        for r0 in range(p0, p1, BKV):
+        for r0 in range(p0, p1, bm):
+            q.add((0, g, r0, min(r0 + bm, p1), 0, 0, 1))
+        for r0 in range(p0, p1, bkv):
             for c in range(kvc):
-                k.add((0, g, r0, min(r0 + BKV, p1), 0, c, kvc))
+                k.add((0, g, r0, min(r0 + bkv, p1), 0, c, kvc))
         for s0, s1 in spans:
-            for r0 in range(s0, s1, BM):
-                q.add((1, g, r0, min(r0 + BM, s1), int(cu_s[owner(r0)]), 0, 1))
-            for r0 in range(s0, s1, BKV):
-                r1 = min(r0 + BKV, s1)
+            for r0 in range(s0, s1, bm):
+                q.add((1, g, r0, min(r0 + bm, s1), int(cu_s[owner(r0)]), 0, 1))
+            for r0 in range(s0, s1, bkv):
+                r1 = min(r0 + bkv, s1)
                 k.add((1, g, r0, r1, int(cu_s[owner(r1 - 1) + 1]), 0, 1))
         m += gs
     return q, k
 
 
-def check_loads(prefix, groups, suffix, q, k, seg, h_q, h_kv, d, dtype):
+def check_loads(prefix, groups, suffix, q, k, seg, h_q, h_kv, d, dtype, bm=128, bkv=128):
     """Every tensor row range the kernels load from a planned tile lies inside its tensor, and every
     buffer range (valid rows of one staged tile x row bytes) stays below 2^31 bytes."""
     cu_p, cu_s, _ = arrays(prefix, groups, suffix)
     tp, ts = int(cu_p[-1]), int(cu_s[-1])
     el = 2 if dtype == "bf16" else 4
-    bq = BQ[dtype]
+    bq, bn = BQ[dtype] if bkv == 128 else 32, BN[bm]
     gm = np.concatenate([[0], np.cumsum(groups)]).astype(np.int64)
     rng_pre = {g: (int(cu_p[g]), int(cu_p[g + 1])) for g in range(len(prefix))}
     rng_suf = {g: (int(cu_s[gm[g]]), int(cu_s[gm[g + 1]])) for g in range(len(prefix))}
@@ -174,8 +173,8 @@ def check_loads(prefix, groups, suffix, q, k, seg, h_q, h_kv, d, dtype):
         rows_ok(row0, row1, ts if kind else tp, "query rows")
         segs = [(p0, row1 if kind == 0 else p1, tp)] + ([(aux, row1, ts)] if kind else [])
         for lo, hi, n in segs:
-            for k0 in range(lo, hi, BN):
-                valid = min(BN, hi - k0)
+            for k0 in range(lo, hi, bn):
+                valid = min(bn, hi - k0)
                 rows_ok(k0, k0 + valid, n, "key tile")
                 assert valid * h_kv * d * el < 2 ** 31
         if kind:
@@ -192,51 +191,59 @@ def check_loads(prefix, groups, suffix, q, k, seg, h_q, h_kv, d, dtype):
                 assert valid * h_q * d * el < 2 ** 31
 
 
-def _planned(planner, prefix, groups, suffix, h_q, h_kv, modes=(0, 1), split=None):
+def _planned(planner, prefix, groups, suffix, h_q, h_kv, d=128, dtype="bf16", tiling=(-1, -1), modes=(0, 1),
+             split=None):
     """Plans of the one-block planner (only where the library uses it: both tile lists within one block)
-    and of the multi-kernel planner; modes=None: the planner the library would run. ``split`` defaults to
-    the library's choice."""
+    and of the multi-kernel planner, for the library's layout of these sizes or a given tiling; modes=None: the
+    planner the library would run. ``split`` defaults to the library's choice."""
     cu_p, cu_s, gsz = arrays(prefix, groups, suffix)
     ng, ns, tp, ts = len(prefix), len(suffix), int(cu_p[-1]), int(cu_s[-1])
-    kvc = kv_chunks_for(ng, tp, ts, h_q, h_kv)
-    split = split_for(ng, tp, ts, h_q) if split is None else split
-    max_q, max_kv = bounds(ng, ns, tp, ts, kvc)
-    one_block = max_q <= 1024 and max_kv <= 1024
+    (lay,) = layouts(planner, [(DTYPES[dtype], ng, ns, tp, ts, h_q, h_kv, d, *tiling)])
+    if split is not None:
+        lay["split"] = split
     if modes is None:
-        modes = (0,) if one_block else (1,)
-    plans = [run_plan(planner, cu_p, cu_s, gsz, ng, ns, tp, ts, mode=mode, kvc=kvc, split=split)
-             for mode in modes if mode == 1 or one_block]
-    return plans, kvc, split
+        modes = (0,) if lay["one_block"] else (1,)
+    plans = [run_plan(planner, cu_p, cu_s, gsz, ng, ns, tp, ts, mode=mode, **{k: lay[k] for k in (
+        "kvc", "split", "max_q", "max_kv", "bm", "bkv")}) for mode in modes if mode == 1 or lay["one_block"]]
+    return plans, lay
 
 
+@pytest.mark.parametrize("tiling", TILINGS)
 @pytest.mark.parametrize("seed,split", [(s, s % 2) for s in range(6)])
-def test_random_groupings_plan_as_the_kernels_assume(planner, seed, split):
+def test_random_groupings_plan_as_the_kernels_assume(planner, seed, split, tiling):
     rng = np.random.default_rng(seed)
     ng = int(rng.integers(1, 40))
     prefix = rng.integers(0, 600, ng) * (rng.random(ng) < 0.8)
     groups = rng.integers(0, 6, ng)
     suffix = rng.integers(0, 400, int(groups.sum())) * (rng.random(int(groups.sum())) < 0.9)
-    (fused, multi), kvc, _ = _planned(planner, prefix, groups, suffix, 8, 2, split=split)
-    assert fused == multi
+    (fused, multi), lay = _planned(planner, prefix, groups, suffix, 8, 2, tiling=tiling, split=split)
+    assert fused == multi and (lay["bm"], lay["bkv"]) == (128 << tiling[1], 128 << tiling[0])
     err, q, k, seg = fused
     assert err == 0
-    eq, ek = expected_tiles(list(prefix), list(groups), list(suffix), kvc, split)
+    eq, ek = expected_tiles(list(prefix), list(groups), list(suffix), lay["kvc"], split, lay["bm"], lay["bkv"])
     assert set(t[:5] + t[6:] for t in q) == eq and len(q) == len(eq)
     assert set(t[:5] + t[6:] for t in k) == ek and len(k) == len(ek)
     for tiles in (q, k):
         work = [t[5] for t in tiles]
         assert work == sorted(work, reverse=True)
-    check_loads(prefix, groups, suffix, q, k, seg, 8, 2, 128, "bf16")
+    check_loads(prefix, groups, suffix, q, k, seg, 8, 2, 128, "bf16", lay["bm"], lay["bkv"])
 
 
 @pytest.mark.parametrize("name", ["tiny", "single_group", "long_prefix", "large_group", "packed_varlen"])
 def test_workload_loads_stay_in_range(planner, name):
+    """With the library's own tiling and with the others its kernels take."""
     wl = WORKLOADS[name]
     prefix, groups, suffix = draw_lengths(wl, 0)
-    plans, _, _ = _planned(planner, prefix, groups, suffix, wl.h_q, wl.h_kv)
-    assert all(p == plans[0] for p in plans) and plans[0][0] == 0
-    _, q, k, seg = plans[0]
-    check_loads(prefix, groups, suffix, q, k, seg, wl.h_q, wl.h_kv, wl.head_dim, wl.dtype)
+    own = None
+    for tiling in [(-1, -1)] + (TILINGS if wl.dtype == "bf16" else []):
+        plans, lay = _planned(planner, prefix, groups, suffix, wl.h_q, wl.h_kv, wl.head_dim, wl.dtype, tiling)
+        if tiling == (-1, -1):
+            own = lay
+        elif lay == own:
+            continue
+        assert all(p == plans[0] for p in plans) and plans[0][0] == 0
+        _, q, k, seg = plans[0]
+        check_loads(prefix, groups, suffix, q, k, seg, wl.h_q, wl.h_kv, wl.head_dim, wl.dtype, lay["bm"], lay["bkv"])
 
 
 def test_fig23_grid_loads_stay_in_range(planner):
@@ -249,8 +256,8 @@ def test_fig23_grid_loads_stay_in_range(planner):
                 S = P // r
                 wl = Workload("grid", 1, G, ("fixed", P), ("uniform", S // 2, S + S // 2), 32, 8, 128, "bf16", 1.0)
                 prefix, groups, suffix = draw_lengths(wl, 0)
-                (plan,), _, _ = _planned(planner, prefix, groups, suffix, 32, 8, modes=None)
-                check_loads(prefix, groups, suffix, plan[1], plan[2], plan[3], 32, 8, 128, "bf16")
+                (plan,), lay = _planned(planner, prefix, groups, suffix, 32, 8, modes=None)
+                check_loads(prefix, groups, suffix, plan[1], plan[2], plan[3], 32, 8, 128, "bf16", lay["bm"], lay["bkv"])
     prefix, groups, suffix = [128], [16], [1024] * 16
-    (plan,), _, _ = _planned(planner, prefix, groups, suffix, 512, 64, modes=None)
-    check_loads(prefix, groups, suffix, plan[1], plan[2], plan[3], 512, 64, 128, "bf16")
+    (plan,), lay = _planned(planner, prefix, groups, suffix, 512, 64, modes=None)
+    check_loads(prefix, groups, suffix, plan[1], plan[2], plan[3], 512, 64, 128, "bf16", lay["bm"], lay["bkv"])

@@ -105,10 +105,16 @@ def test_hazard_check_sees_planted_mistakes():
     assert hazards(ok + ["\tscratch_load_dword v1, off, off"])[0]
 
 
-def test_cases_choose_the_wide_kernels():
-    # the rules of use_wide() and use_wide_q() in pg_attn.hip, restated on the test sizes
-    for (p, _, s), hq, _, d, _ in DQ_CASES:
-        assert d == 128 and sum(p) // 8192 >= len(p) and (-(-sum(p) // 256) - (-sum(s) // 256)) * hq >= 512, (p, s)
-    for (p, _, s), hq, hkv, _, _ in CASES + DQ_CASES:
-        tp, ts, ng = sum(p), sum(s), len(p)
-        assert tp // 1024 >= ng and hq / hkv * (0.5 * tp + ts) / (ng * 32) * -(-tp // 256) * hkv >= 80 * 256, (p, s)
+def test_cases_choose_the_wide_kernels(tmp_path_factory):
+    """Read from the library's own rules (pg_layout.hpp), compiled for the host."""
+    from tests.test_plan_host import DTYPES, build_planner, layouts
+    exe = build_planner(tmp_path_factory)
+
+    def tiles(dtype, case):
+        (p, _, s), hq, hkv, d, _ = case
+        (lay,) = layouts(exe, [(DTYPES[dtype], len(p), len(s), sum(p), sum(s), hq, hkv, d)])
+        return lay["bm"], lay["bkv"]
+
+    assert all(tiles("bf16", c) == (128, 256) for c in CASES)
+    assert all(tiles("bf16", c) == (256, 256) for c in DQ_CASES)
+    assert all(tiles("fp32", c) == (128, 128) for c in CASES + DQ_CASES)
