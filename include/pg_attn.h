@@ -80,9 +80,10 @@ typedef enum {
 size_t pg_attn_fwd_workspace_size(int n_groups, int n_suffixes, int total_prefix, int total_suffix, int h_q,
                                   int h_kv, int head_dim);
 
-/* Workspace bytes pg_attn_bwd needs for these sizes (host call, no GPU use; 0 for negative sizes). It holds
- * the tile plan, two float values per query row and head (rowsum(dO*O) and the log-sum-exp) and, when the walks of long prefix key tiles are split over several workgroups,
- * their fp32 dK/dV partial sums. */
+/* Workspace bytes pg_attn_bwd needs for these sizes in either dtype (host call, no GPU use; 0 for negative
+ * sizes). It holds the tile plan, rowsum(dO*O) of every query row and head (4 bytes each; as much again for their
+ * log-sum-exp where a bf16 call takes the 256-key dK/dV kernel) and, when the walks of long prefix key tiles are
+ * split over several workgroups, their fp32 dK/dV partial sums (8 * total_prefix * h_kv * head_dim bytes a piece). */
 size_t pg_attn_bwd_workspace_size(int n_groups, int n_suffixes, int total_prefix, int total_suffix, int h_q,
                                   int h_kv, int head_dim);
 

@@ -110,9 +110,10 @@ inline Layout bwd_layout(int dtype, int ng, int ns, int tp, int ts, int h_q, int
                      use_wide_q(dtype, ng, tp, ts, h_q, d));
 }
 
+// Bytes for a backward of these sizes in either type (the query does not know which).
 inline size_t bwd_workspace(int ng, int ns, int tp, int ts, int h_q, int h_kv, int d) {
-  return std::max(make_layout(ng, ns, tp, ts, h_q, h_kv, d, true).total,
-                  make_layout(ng, ns, tp, ts, h_q, h_kv, d, true, true).total);
+  return std::max(bwd_layout(PG_BF16, ng, ns, tp, ts, h_q, h_kv, d).total,
+                  bwd_layout(PG_FP32, ng, ns, tp, ts, h_q, h_kv, d).total);
 }
 
 // Whether plan_fused_kernel plans the call: every tile list fits its one block.

@@ -86,6 +86,25 @@ def arrays(prefix, groups, suffix):
     return cu_p, cu_s, np.asarray(groups, np.int64)
 
 
+def test_workspace_query_is_what_one_of_the_types_needs(planner):
+    """pg_attn_bwd_workspace_size is the larger of the two types' needs, and the 128-key layout alone where no
+    type takes the 256-key kernel: 17 groups of 1000 rows (whose size a second tiling raised from 3 to 274 MB)."""
+    rng = np.random.default_rng(11)
+    calls = [(17, 68, 17000, 4096, 32, 8, 128)]
+    for _ in range(300):
+        h_kv = int(rng.choice([1, 2, 4, 8]))
+        ng = int(rng.integers(1, 20))
+        calls.append((ng, ng * int(rng.integers(0, 20)), int(10 ** rng.uniform(0, 5)), int(10 ** rng.uniform(0, 5.3)),
+                      h_kv * int(rng.choice([1, 4, 8])), h_kv, int(rng.choice([64, 128]))))
+    bf16, fp32 = (layouts(planner, [(t, *c) for c in calls]) for t in (0, 1))
+    narrow = layouts(planner, [(0, *c, 0, 0) for c in calls])
+    assert {lay["bkv"] for lay in bf16} == {128, 256} and all(lay["bkv"] == 128 for lay in fp32)
+    for a, b, n in zip(bf16, fp32, narrow):
+        assert a["size_query"] == b["size_query"] == max(a["workspace"], b["workspace"])
+        assert a["bkv"] == 256 or a["size_query"] == n["workspace"]
+    assert bf16[0]["bkv"] == 128
+
+
 @pytest.mark.parametrize("gsz,ns", [
     # 32-bit sums that wrap around to n_suffixes (the planner would then index cu_suffix_lens with
     # member starts near 2^31)
