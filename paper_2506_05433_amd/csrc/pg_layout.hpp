@@ -25,6 +25,11 @@ struct Layout {
   int bm;   // query rows per query tile: kFwdBM, or kWideBM for the 256-row kernels
 };
 
+// Mean walk of a prefix key tile for 256-key tiles, in steps (32 query rows x 256 keys), from the mean group.
+inline double wide_walk(int ng, int tp, int ts, int h_q, int h_kv) {
+  return (double)(h_q / h_kv) * (0.5 * tp + ts) / ((double)(ng > 0 ? ng : 1) * kWideBQ);
+}
+
 // Pieces each prefix key tile's query walk is split into for the dK/dV kernel: enough
 // workgroups to balance the long prefix walks over the CUs (about 512 prefix pieces, i.e.
 // two per CU), at most 8, and 1 when there are already that many prefix key tiles. More
@@ -33,19 +38,37 @@ struct Layout {
 // least 16 64-row query tiles of the average walk (a group's rows, once per query head of
 // the kv head): shorter pieces cost more in their fixed start-up and in the reduce launch
 // than they save. A grid of at most 128 key tiles (half the CUs) runs as long as its
-// longest walk whatever the total work, so there pieces of one such tile pay off. With 256-key
-// tiles (one workgroup per CU) about 384 pieces are best, and two up to 768: one group of P 4096,
-// 32/8 heads (136 tiles) takes 913, 909, 1050, 982 us with 2, 3, 4, 6 pieces, P 16384 (520 tiles)
-// 6.30 ms with one and 6.17 with two.
-inline int kv_chunks_for(int ng, int tp, int ts, int h_q, int h_kv, int bkv) {
-  if (tp <= 0 || h_kv <= 0) return 1;
-  const long tiles = (ceil_div_l(tp, bkv) + ng) * (long)h_kv;
+// longest walk whatever the total work, so there pieces of one such tile pay off.
+inline int kv_chunks_narrow(int ng, int tp, int ts, int h_q, int h_kv) {
+  const long tiles = (ceil_div_l(tp, kKvBN) + ng) * (long)h_kv;
   long c = ceil_div_l(512, tiles);
-  if (bkv == kWideBN) c = tiles >= 768 ? 1 : std::max(2L, ceil_div_l(384, tiles));
   const long walk = ceil_div_l((long)tp + ts, (long)(ng > 0 ? ng : 1) * 64) * (h_q / h_kv);
   const long min_piece = 2 * tiles <= 256 ? 1 : 16;
   if (c > walk / min_piece) c = walk / min_piece;
   return (int)(c < 1 ? 1 : (c > 8 ? 8 : c));
+}
+
+// The same for 256-key tiles, which run one workgroup per CU. Where there is more than one, each piece costs
+// 8 * total_prefix * h_kv * head_dim bytes of workspace. Measured on 660 random shapes (1..16 groups, 1..8 kv heads,
+// 1..8 query heads each, both head dims), us of dK/dV and its reduction at 1, 2, .. pieces:
+// * up to about 400 tiles the longest walk or a nearly empty last round sets the time, and about 384 pieces are
+//   best: 106 tiles 2326, 1286, 949, 777 and 843 at five; 214 tiles 1658, 948; 388 tiles 2267, 1753;
+// * above, one piece does as well (mean ratio of one to two 0.98 for walks of 260..1000 steps, 1.02 beyond) and
+//   needs no partial sums, but for tiles just above two per CU with long walks: 544 tiles 7769, 6758; 560 tiles
+//   6014, 5488. At 720 tiles (5077, 4737) two pieces would take 376 MB, at 512 (P 16384, 32/8 heads: 2%) 268 MB;
+// * a piece of few steps does not pay for its start-up and partial sums (fewer than 50 steps, or 150 where the tiles
+//   fill the CUs anyway): 432 tiles of 121 steps 453, 545; 652 tiles of 75 steps 394, 509.
+inline int kv_chunks_wide(int ng, int tp, int ts, int h_q, int h_kv) {
+  const long least = ceil_div_l(tp, kWideBN) * (long)h_kv, tiles = least + (long)ng * h_kv;
+  const bool few = tiles <= 400;
+  const long c = few || (least > 512 && tiles <= 640) ? std::max(2L, ceil_div_l(384, tiles)) : 1;
+  const long most = (long)(wide_walk(ng, tp, ts, h_q, h_kv) / (few ? 50 : 150));
+  return (int)std::max(1L, std::min({c, most, 8L}));
+}
+
+inline int kv_chunks_for(int ng, int tp, int ts, int h_q, int h_kv, int bkv) {
+  if (tp <= 0 || h_kv <= 0) return 1;
+  return bkv == kWideBN ? kv_chunks_wide(ng, tp, ts, h_q, h_kv) : kv_chunks_narrow(ng, tp, ts, h_q, h_kv);
 }
 
 // Problems whose stacked query tiles x heads cannot fill the 256 CUs tile each member's
@@ -60,8 +83,7 @@ constexpr long kSplitBelow = 256;
 // 335 -> 297 us, 232 steps 718 -> 675 us; 184 steps but prefixes of 300 rows 540 -> 608 us.
 inline bool use_wide(int dtype, int ng, int tp, int ts, int h_q, int h_kv) {
   if (dtype != PG_BF16 || ng <= 0 || h_kv <= 0 || tp / 1024 < ng) return false;
-  const double walk = (double)(h_q / h_kv) * (0.5 * tp + ts) / ((double)ng * kWideBQ);
-  return walk * (double)ceil_div_l(tp, kWideBN) * h_kv >= 80.0 * 256.0;
+  return wide_walk(ng, tp, ts, h_q, h_kv) * (double)ceil_div_l(tp, kWideBN) * h_kv >= 80.0 * 256.0;
 }
 
 // Whether the backward runs dq_wide_kernel (256-row query tiles). Its workgroups have a CU to themselves,

@@ -105,6 +105,23 @@ def test_workspace_query_is_what_one_of_the_types_needs(planner):
     assert bf16[0]["bkv"] == 128
 
 
+@pytest.mark.parametrize("ng,ns,tp,ts,h_q,h_kv,d,pieces", [
+    # (sizes, pieces of a prefix walk with 256-key tiles): on both sides of each line of kv_chunks_wide
+    (1, 8, 13367, 1407, 8, 2, 128, 4),
+    (1, 8, 4096, 5120, 32, 8, 128, 3),
+    (3, 6, 24635, 657, 16, 4, 128, 2),      # 388..400 tiles
+    (1, 16, 16384, 5120, 32, 8, 128, 1),    # 512: two whole rounds
+    (2, 32, 17576, 7824, 40, 8, 128, 2),    # 552..568: just above them
+    (2, 6, 22928, 224, 40, 8, 128, 1),      # 720
+    (7, 434, 13080, 20622, 8, 8, 128, 1),   # one query head per kv head: short walks, cut in two they ran 20% longer
+    (10, 100, 40758, 3595, 4, 4, 128, 1),   # the same, 30%
+    (6, 66, 30268, 4338, 2, 2, 128, 2),     # short walks, but fewer tiles than CUs
+])
+def test_pieces_of_the_256_key_walks(planner, ng, ns, tp, ts, h_q, h_kv, d, pieces):
+    (lay,) = layouts(planner, [(0, ng, ns, tp, ts, h_q, h_kv, d, 1, 0)])
+    assert lay["kvc"] == pieces and lay["bkv"] == 256
+
+
 @pytest.mark.parametrize("gsz,ns", [
     # 32-bit sums that wrap around to n_suffixes (the planner would then index cu_suffix_lens with
     # member starts near 2^31)
