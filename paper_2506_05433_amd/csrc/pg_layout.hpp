@@ -77,13 +77,22 @@ inline int kv_chunks_for(int ng, int tp, int ts, int h_q, int h_kv, int bkv) {
 constexpr long kSplitBelow = 256;
 
 // Whether the backward runs dkdv_wide_kernel (256-key tiles). It does the same work in fewer, longer
-// workgroups, so it needs enough of it: at least 80 tile steps (32 query rows x 256 keys) per CU in the
-// prefix walks, and prefixes long enough that a tile's 256 keys are rarely ragged. Measured (dK/dV
-// plus reduction, dkdv_kernel -> wide): 24 steps per CU 112 -> 123 us, 55 steps 194 -> 203 us, 112 steps
-// 335 -> 297 us, 232 steps 718 -> 675 us; 184 steps but prefixes of 300 rows 540 -> 608 us.
+// workgroups, one per CU. Measured (dK/dV plus reduction, dkdv_kernel -> wide, us):
+// * it needs work: at least 80 steps (32 query rows x 256 keys) per CU in the prefix walks. 24 steps 112 -> 123, 55
+//   194 -> 203, 112 335 -> 297, 232 718 -> 675;
+// * and pieces that share it: with few tiles the eight pieces a walk may have leave CUs idle while the longest ones
+//   run, so no piece may take 1.5 times as long as all of them spread over the CUs. 5/1 heads, P 2440, 10 tiles
+//   334 -> 515; 8/1, P 7653, d 64, 30 tiles 249 -> 320; the other side: 8/1, P 12122, 48 tiles 846 -> 697;
+// * the line at prefixes of 1024 rows on average (ragged 256-key tiles below) is on the safe side: mean 300 rows
+//   540 -> 608, but 773 rows, 488 tiles 4104 -> 3826 and 966 rows, d 64, 464 tiles 2313 -> 2236; above it 1451 rows
+//   3842 -> 3505.
+// Over 563 random shapes on this side of the lines it takes 0.89 of dkdv_kernel's time; 26 of them lose more than
+// 1.5%, most of those with 64-wide heads and about 100 steps per CU (the worst 175 -> 219).
 inline bool use_wide(int dtype, int ng, int tp, int ts, int h_q, int h_kv) {
   if (dtype != PG_BF16 || ng <= 0 || h_kv <= 0 || tp / 1024 < ng) return false;
-  return wide_walk(ng, tp, ts, h_q, h_kv) * (double)ceil_div_l(tp, kWideBN) * h_kv >= 80.0 * 256.0;
+  const double walk = wide_walk(ng, tp, ts, h_q, h_kv), longest = walk * ((double)tp + ts) / (0.5 * tp + ts);
+  const double per_cu = walk * (double)ceil_div_l(tp, kWideBN) * h_kv / 256;
+  return per_cu >= 80 && longest / kv_chunks_for(ng, tp, ts, h_q, h_kv, kWideBN) <= 1.5 * per_cu;
 }
 
 // Whether the backward runs dq_wide_kernel (256-row query tiles). Its workgroups have a CU to themselves,

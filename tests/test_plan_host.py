@@ -122,6 +122,21 @@ def test_pieces_of_the_256_key_walks(planner, ng, ns, tp, ts, h_q, h_kv, d, piec
     assert lay["kvc"] == pieces and lay["bkv"] == 256
 
 
+@pytest.mark.parametrize("ng,ns,tp,ts,h_q,h_kv,d,keys", [
+    # on both sides of each line of use_wide
+    (1, 52, 2440, 17456, 5, 1, 128, 128),   # 10 tiles, eight pieces each: 334 us, with 256 keys 515
+    (1, 53, 7653, 2290, 8, 1, 64, 128),     # 30 tiles: 249, 320
+    (1, 55, 12122, 1742, 8, 1, 128, 256),   # 48 tiles: 846, 697
+    (17, 68, 17000, 4096, 32, 8, 128, 128),  # prefixes of 1000 rows
+    (9, 72, 13059, 29013, 32, 8, 128, 256),  # of 1451
+    (1, 5, 1024, 1000, 32, 8, 128, 128),    # 24 steps per CU
+    (1, 8, 2048, 5120, 32, 8, 128, 256),
+])
+def test_choice_of_the_256_key_kernel(planner, ng, ns, tp, ts, h_q, h_kv, d, keys):
+    (lay,) = layouts(planner, [(0, ng, ns, tp, ts, h_q, h_kv, d)])
+    assert lay["bkv"] == keys
+
+
 @pytest.mark.parametrize("gsz,ns", [
     # 32-bit sums that wrap around to n_suffixes (the planner would then index cu_suffix_lens with
     # member starts near 2^31)
