@@ -88,10 +88,10 @@ __global__ void __launch_bounds__(kPlanThreads) plan_last_fused_kernel(
   const int t = threadIdx.x;
   const int members = ok && t < ng ? lds.gi[t].m1 - lds.gi[t].m0 : 0;
   const int nb = (members + mpw - 1) / mpw;
-  lds.nq[t] = nb;
-  __syncthreads();
+  int below[1] = {nb};
+  block_exclusive_sums(below, ng, lds.tot + 3);
   if (t > ng) return;
-  const int first = sum_below<int>(lds.nq, t, ng);
+  const int first = below[0];
   for (int k = 0; k < nb; ++k)
     if (first + k < nb_max) {
       LastBlock b;

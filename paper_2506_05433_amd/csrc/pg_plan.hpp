@@ -156,18 +156,21 @@ __device__ inline void plan_groups_body(const int* __restrict__ cu_p, const int*
 
 // Grouping arrays small enough for LDS (the usual case) are planned from there. The one-block steps are
 // all latency: every dependent global load costs 0.5 to 1 us and a 1024-wide scan twenty barriers, so the
-// arrays are loaded once, side by side, searched in LDS, and each thread sums its own prefix instead of
-// scanning. Measured (plan_fused_kernel): 1 group of 4 members, 6 tiles 10.8 -> 6.3 us; 7 groups of 6
-// (6210 + 19050 rows, about 400 key tiles) 19.5 -> 11.0 us, of which the ranks took half before their
-// comparisons were shared out and cut to four instructions; plan_groups_kernel, 8 groups of 16, 10.0 -> 5.1 us.
+// arrays are loaded once, side by side, searched in LDS, and summed by wave scans (one barrier, or none up to 63
+// groups). Measured, plan_groups_kernel (the rotary embedding's plan), from memory -> from LDS: 1 group 9.9 -> 6.2
+// us, 100 groups 9.9 -> 6.6, 1000 groups 11.2 -> 8.4; with each thread adding up the entries before its own instead
+// 6.2, 11.7, 91.7 (the sums are the only step that grows with the square of the groups, so they stay scans).
+// plan_fused_kernel: 1 group of 4 members, 6 tiles 10.8 -> 6.3 us; 7 groups of 6 (6210 + 19050 rows, about 400
+// key tiles) 19.5 -> 11.0 us, of which the ranks took half before their comparisons were shared out and cut to
+// four instructions.
 constexpr int kLdsGroups = kPlanThreads - 1;  // one thread per group, and one for the totals
 constexpr int kLdsMembers = 4096;
 
 __host__ __device__ inline bool plan_fits_lds(int ng, int ns) { return ng <= kLdsGroups && ns <= kLdsMembers; }
 
 struct PlanLds {
-  alignas(16) int gsz[kLdsGroups + 1], nq[kLdsGroups + 1], nkv[kLdsGroups + 1];
   alignas(16) int work[2][kPlanThreads];  // the tiles' ranking keys, -1 past the last tile
+  alignas(16) int tot[4][kPlanThreads / 64];  // sums of each wave, one row per prefix sum
   int part[kPlanThreads];                 // partial ranks
   int cu_p[kLdsGroups + 1], cu_s[kLdsMembers + 1], qoff[kLdsGroups + 1], kvoff[kLdsGroups + 1];
   GroupInfoEx gi[kLdsGroups + 1];
@@ -178,17 +181,38 @@ struct alignas(16) Int4 {
   int v[4];
 };
 
-// Sum of a[0 .. i) for i <= n (a is 16-byte aligned and readable to a multiple of four).
-template <typename V>
-__device__ inline V sum_below(const int* a, int i, int n) {
-  V s = 0;
-#pragma unroll 4
-  for (int k = 0; k < n; k += 4) {
-    const Int4 x = *(const Int4*)(a + k);
+// Exclusive prefix sums over the block of N values per thread, of which only those of the first n threads may be
+// nonzero; results are meant for threads 0 .. n. A wave scan, then the sums of the waves before (tot, N rows of
+// one entry per wave, not used again by the caller before a barrier); up to 63 values need neither barrier nor tot.
+template <int N>
+__device__ __forceinline__ void block_exclusive_sums(int (&v)[N], int n, int (*tot)[kPlanThreads / 64]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int x[N];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s += k + e < i ? x.v[e] : 0;
+  for (int k = 0; k < N; ++k) x[k] = v[k];
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int y = __shfl_up(x[k], off);
+      x[k] += lane >= off ? y : 0;
+    }
+  if (n >= 64) {
+    if (lane == 63)
+#pragma unroll
+      for (int k = 0; k < N; ++k) tot[k][wave] = x[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int w = 0; w < kPlanThreads / 64; w += 4) {
+        const Int4 q = *(const Int4*)(tot[k] + w);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[k] += w + e < wave ? q.v[e] : 0;
+      }
   }
-  return s;
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = x[k] - v[k];
 }
 
 // plan_groups_body for arrays that fit PlanLds: the same checks, ranges and offsets. Leaves copies of
@@ -202,8 +226,9 @@ __device__ inline bool plan_groups_lds(const int* __restrict__ cu_p, const int* 
   if (t <= ng) sh.cu_p[t] = cu_p[t];
   const int size = t < ng ? gsz[t] : 0;
   // sizes out of range are an error; they are kept out of the sums, whose results are used as indices
+  // (and which fit 32 bits: at most kLdsGroups sizes of at most kLdsMembers)
   const bool bad_size = size < 0 || size > ns;
-  sh.gsz[t] = bad_size ? 0 : size;
+  const int members = bad_size ? 0 : size;
   if (t == 0) sh.err = 0;
   __syncthreads();
   int bad = bad_size;
@@ -215,17 +240,18 @@ __device__ inline bool plan_groups_lds(const int* __restrict__ cu_p, const int* 
     const int v = sh.cu_s[m];
     if ((m == 0 && v != 0) || (m == ns && v != ts) || (m > 0 && v < sh.cu_s[m - 1])) bad = 1;
   }
-  // member starts, in 64 bits so that no sum of sizes can wrap around to n_suffixes
-  const long long m0 = t <= ng ? sum_below<long long>(sh.gsz, t, ng) : 0;
-  if ((t == ng && m0 != ns) || m0 + sh.gsz[t] > ns) bad = 1;
+  int start[1] = {members};
+  block_exclusive_sums(start, ng, sh.tot);
+  const int m0 = start[0];
+  if (t <= ng && ((t == ng && m0 != ns) || m0 + members > ns)) bad = 1;
   if (bad) atomicOr(&sh.err, 1);
   __syncthreads();
   const bool ok = !sh.err;
-  int nq = 0, nkv = 0;
+  int n[2] = {0, 0};  // query and key tiles
   if (ok && t < ng) {
     GroupInfoEx gi;
-    gi.m0 = (int)m0;
-    gi.m1 = (int)m0 + sh.gsz[t];
+    gi.m0 = m0;
+    gi.m1 = m0 + members;
     gi.p0 = sh.cu_p[t];
     gi.p1 = sh.cu_p[t + 1];
     gi.s0 = sh.cu_s[gi.m0];
@@ -233,19 +259,16 @@ __device__ inline bool plan_groups_lds(const int* __restrict__ cu_p, const int* 
     gi.pad0 = gi.pad1 = 0;
     sh.gi[t] = gi;
     ginfo[t] = gi;
-    nq = ceil_div(gi.p1 - gi.p0, bm) + response_tiles(sh.cu_s, gi, bm, split);
-    nkv = ceil_div(gi.p1 - gi.p0, bkv) * kv_chunks + response_tiles(sh.cu_s, gi, bkv, split);
+    n[0] = ceil_div(gi.p1 - gi.p0, bm) + response_tiles(sh.cu_s, gi, bm, split);
+    n[1] = ceil_div(gi.p1 - gi.p0, bkv) * kv_chunks + response_tiles(sh.cu_s, gi, bkv, split);
   }
-  sh.nq[t] = nq;
-  sh.nkv[t] = nkv;
-  __syncthreads();
+  block_exclusive_sums(n, ng, sh.tot + 1);
   if (t <= ng) {
-    const int oq = sum_below<int>(sh.nq, t, ng), ok_ = sum_below<int>(sh.nkv, t, ng);
-    sh.qoff[t] = oq;
-    sh.kvoff[t] = ok_;
+    sh.qoff[t] = n[0];
+    sh.kvoff[t] = n[1];
     // the host sized the tile arrays from the totals; a list longer than that bound can only come
     // from inconsistent arrays, so it is treated as an error too
-    if (t == ng && ok && (oq > max_q || ok_ > max_kv)) sh.err = 1;
+    if (t == ng && ok && (n[0] > max_q || n[1] > max_kv)) sh.err = 1;
   }
   __syncthreads();
   const bool good = !sh.err;

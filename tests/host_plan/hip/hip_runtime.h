@@ -6,6 +6,7 @@
 #pragma once
 #include <algorithm>
 #include <barrier>
+#include <memory>
 #include <thread>
 #include <vector>
 
@@ -26,6 +27,22 @@ inline std::barrier<>* g_block_barrier = nullptr;
 
 inline void __syncthreads() { g_block_barrier->arrive_and_wait(); }
 inline int atomicOr(int* p, int v) { return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
+
+// Lane exchange within a wave of 64: every thread of the wave takes part.
+struct HostWave {
+  std::barrier<> meet{64};
+  int v[64];
+};
+inline HostWave* g_waves = nullptr;
+inline int __shfl_up(int v, unsigned delta) {
+  HostWave& w = g_waves[threadIdx.x / 64];
+  const unsigned lane = threadIdx.x % 64;
+  w.v[lane] = v;
+  w.meet.arrive_and_wait();
+  const int r = lane >= delta ? w.v[lane - delta] : v;
+  w.meet.arrive_and_wait();
+  return r;
+}
 using std::max;
 using std::min;
 
@@ -36,6 +53,8 @@ void host_launch(unsigned grid, unsigned threads, F body) {
   blockDim.x = threads;
   std::barrier<> bar((std::ptrdiff_t)threads);
   g_block_barrier = &bar;
+  const std::unique_ptr<HostWave[]> waves(new HostWave[(threads + 63) / 64]);
+  g_waves = waves.get();
   std::vector<std::thread> ts;
   ts.reserve(threads);
   for (unsigned t = 0; t < threads; ++t)

@@ -55,3 +55,33 @@ def test_plan_from_lds_matches_plan_from_memory(line, dtype):
     assert a["o_pre"].shape == b["o_pre"].shape and np.isfinite(a["o_suf"]).all()
     for k in a:
         assert np.array_equal(a[k], b[k]), f"{k}: the two plans gave different results"
+
+
+def _plan_us(call):
+    from paper_2506_05433_amd import binding
+    best = float("inf")
+    for _ in range(3):
+        torch.cuda.synchronize()
+        binding.timing_start()
+        for _ in range(10):
+            call()
+        torch.cuda.synchronize()
+        binding.timing_stop()
+        n, ms = binding.timing_get("plan")
+        best = min(best, ms / n * 1e3)
+    return best
+
+
+def test_planning_from_lds_is_no_slower_than_from_memory():
+    """At its largest size, where sums that walk all groups in every thread took 93 us (8.6 us with scans, 11.5 us
+    from memory)."""
+    from paper_2506_05433_amd import binding
+    p, g, s = _lengths(1023, 1023, 3)
+    times = []
+    for lengths in ((p, g, s), (p + (0,), g + (0,), s)):
+        dev = binding.to_device(make_problem("single_group", seed=731, lengths=lengths, h_q=2, h_kv=2, head_dim=64), "cuda")
+        args = (dev["q_pre"], dev["q_suf"], dev["k_pre"], dev["k_suf"], dev["cu_prefix"], dev["cu_suffix"],
+                dev["group_sizes"])
+        times.append(_plan_us(lambda: binding.rope(*args)))
+    print(f"[plan lds] inside {times[0]:.1f} us, outside {times[1]:.1f} us", flush=True)
+    assert times[0] <= 1.5 * times[1], times

@@ -280,6 +280,20 @@ def test_random_groupings_plan_as_the_kernels_assume(planner, seed, split, tilin
     check_loads(prefix, groups, suffix, q, k, seg, 8, 2, 128, "bf16", lay["bm"], lay["bkv"])
 
 
+@pytest.mark.parametrize("ng", [1, 62, 63, 64, 65, 128, 500])
+def test_group_counts_around_a_wave(planner, ng):
+    """The prefix sums over groups within one wave, and from one wave to the next."""
+    rng = np.random.default_rng(ng)
+    prefix, groups = rng.integers(0, 300, ng), rng.integers(0, 3, ng)
+    suffix = rng.integers(0, 200, int(groups.sum()))
+    plans, lay = _planned(planner, prefix, groups, suffix, 4, 4, split=0)
+    assert (len(plans) == 2) == (ng <= 128)
+    eq, ek = expected_tiles(list(prefix), list(groups), list(suffix), lay["kvc"])
+    for err, q, k, _ in plans:
+        assert err == 0 and set(t[:5] + t[6:] for t in q) == eq and len(q) == len(eq)
+        assert set(t[:5] + t[6:] for t in k) == ek and len(k) == len(ek)
+
+
 @pytest.mark.parametrize("name", ["tiny", "single_group", "long_prefix", "large_group", "packed_varlen"])
 def test_workload_loads_stay_in_range(planner, name):
     """With the library's own tiling and with the others its kernels take."""
