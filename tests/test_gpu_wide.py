@@ -2,8 +2,9 @@
 
 The sizes are large enough for the library to choose them (test_wide_codegen.py checks the choice) and
 ragged everywhere: prefixes one row past a key tile, responses shorter than a query tile, a key tile spanning
-several members, empty responses, a group without members, GQA ratios 1, 4 and 8, both head dims and both
-layouts. Tolerances are those of every bf16 parity test (tests/_parity.py).
+several members, empty responses and prefixes, a group without members, GQA ratios 1 to 8, both head dims and both
+layouts, with response rows before a prefix in the single buffer. Tolerances are those of every bf16 parity test
+(tests/_parity.py).
 """
 import numpy as np
 import pytest
@@ -23,12 +24,18 @@ CASES = [
     (((1025,), (10,), RAGGED), 64, 8, 64, 2),
     (((1500, 1100), (10, 0), RAGGED), 64, 8, 128, 7),
     (((1281, 1024), (3, 10), (257, 1, 3200) + RAGGED), 32, 32, 64, 31),
+    # response rows before a prefix (a prefix offset in the single buffer), an empty prefix beside a long one
+    (((1100, 1300), (4, 6), RAGGED), 64, 8, 64, 4),
+    (((2100, 0, 1200), (3, 4, 3), RAGGED), 64, 8, 128, 1),
+    # one head: too few tiles to fill the CUs, so each member's rows are tiled on their own
+    (((16380,), (5,), (3000, 1, 700, 2491, 2000)), 1, 1, 64, 0),
 ]
 
 # the dQ kernel as well: prefixes of 8192 rows and more
 DQ_CASES = [
     (((8193,), (10,), RAGGED), 16, 16, 128, 3),
     (((8192, 8479), (0, 11), (5,) + RAGGED), 16, 8, 128, 6),
+    (((8193, 8479), (4, 7), (5,) + RAGGED), 16, 8, 128, 2),
 ]
 
 
@@ -42,6 +49,16 @@ def test_wide_backward(case):
 
 
 @pytest.mark.parametrize("which", [CASES[0], DQ_CASES[1]], ids=["dkdv", "dq"])
+def test_wide_backward_with_peaked_softmax(which):
+    """Q x 4: sharp rows, whose dP - Dsum is small beside the Dsum that dP starts at."""
+    lengths, hq, hkv, d, kv = which
+    r = hq // hkv
+    prob = make_problem("single_group", seed=705, lengths=lengths, h_q=hq, h_kv=hkv, head_dim=d, peaked=True)
+    _full_compare(prob, heads=list(range(kv * r, (kv + 1) * r)), kv_heads=[kv])
+
+
+@pytest.mark.parametrize("which", [CASES[0], CASES[4], CASES[5], DQ_CASES[1], DQ_CASES[2]],
+                         ids=["dkdv", "dkdv_offset_d64", "dkdv_empty_prefix", "dq", "dq_offset"])
 def test_wide_backward_xours_and_repeat(which):
     lengths, hq, hkv, d, _ = which
     prob = make_problem("single_group", seed=710, lengths=lengths, h_q=hq, h_kv=hkv, head_dim=d)

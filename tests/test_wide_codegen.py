@@ -113,6 +113,7 @@ def test_cases_choose_the_wide_kernels(tmp_path_factory):
     def tiles(dtype, case):
         (p, _, s), hq, hkv, d, _ = case
         (lay,) = layouts(exe, [(DTYPES[dtype], len(p), len(s), sum(p), sum(s), hq, hkv, d)])
+        assert lay["split"] == (hq == 1)  # member-aligned tiles in the one-head case only
         return lay["bm"], lay["bkv"]
 
     assert all(tiles("bf16", c) == (128, 256) for c in CASES)
