@@ -485,4 +485,72 @@ __global__ void __launch_bounds__(kPlanThreads) plan_fused_kernel(
   }
 }
 
+// ---------------------------------------------------------------- final-token call (pg_last.hpp)
+// A run of a group's members whose final queries share a workgroup.
+struct LastBlock {
+  int group, m_first, m_count, pad;
+};
+
+// Member blocks: group g's members in runs of at most mpw, groups in order (one block of
+// kPlanThreads threads; groups processed in passes with a running offset).
+__global__ void __launch_bounds__(kPlanThreads) plan_last_kernel(const PlanHeader* hdr, const GroupInfoEx* ginfo,
+                                                                 int ng, int mpw, int nb_max, LastBlock* blocks,
+                                                                 int* n_blocks) {
+  __shared__ int tmp[kPlanThreads];
+  __shared__ int carry;
+  const int t = threadIdx.x;
+  if (t == 0) carry = 0;
+  __syncthreads();
+  const bool ok = !hdr->error;
+  for (int base = 0; base < ng; base += kPlanThreads) {
+    const int g = base + t;
+    const int members = (g < ng && ok) ? ginfo[g].m1 - ginfo[g].m0 : 0;
+    const int nb = (members + mpw - 1) / mpw;
+    const int inc = block_inclusive_scan<kPlanThreads>(nb, tmp);
+    const int first = carry + inc - nb;
+    for (int k = 0; k < nb; ++k) {
+      if (first + k < nb_max) {
+        LastBlock b;
+        b.group = g;
+        b.m_first = ginfo[g].m0 + k * mpw;
+        b.m_count = min(mpw, members - k * mpw);
+        b.pad = 0;
+        blocks[first + k] = b;
+      }
+    }
+    __syncthreads();
+    if (t == kPlanThreads - 1) carry += inc;
+    __syncthreads();
+  }
+  if (t == 0) *n_blocks = ok ? min(carry, nb_max) : 0;
+}
+
+// The planner's groups and the member blocks in one launch, for grouping arrays that fit LDS: the calls
+// this serves are short (one text of 4096 rows and 8 questions: the two launches were 10.8 of 26 us).
+__global__ void __launch_bounds__(kPlanThreads) plan_last_fused_kernel(
+    const int* __restrict__ cu_p, const int* __restrict__ cu_s, const int* __restrict__ gsz, int ng, int ns, int tp,
+    int ts, int bm, int bkv, PlanHeader* hdr, GroupInfoEx* ginfo, int* qoff, int* kvoff, int mpw, int nb_max,
+    LastBlock* blocks, int* n_blocks) {
+  __shared__ PlanLds lds;
+  const bool ok = plan_groups_lds(cu_p, cu_s, gsz, ng, ns, tp, ts, bm, bkv, 1, 0, 0x7fffffffL, 0x7fffffffL, hdr, ginfo,
+                                  qoff, kvoff, lds);
+  const int t = threadIdx.x;
+  const int members = ok && t < ng ? lds.gi[t].m1 - lds.gi[t].m0 : 0;
+  const int nb = (members + mpw - 1) / mpw;
+  int below[1] = {nb};
+  block_exclusive_sums(below, ng, lds.tot + 3);
+  if (t > ng) return;
+  const int first = below[0];
+  for (int k = 0; k < nb; ++k)
+    if (first + k < nb_max) {
+      LastBlock b;
+      b.group = t;
+      b.m_first = lds.gi[t].m0 + k * mpw;
+      b.m_count = min(mpw, members - k * mpw);
+      b.pad = 0;
+      blocks[first + k] = b;
+    }
+  if (t == ng) *n_blocks = ok ? min(first, nb_max) : 0;
+}
+
 }  // namespace pg

@@ -7,11 +7,13 @@
 //        kv_chunks, split, max_q, max_kv, then cu_prefix_lens[ng+1], cu_suffix_lens[ns+1],
 //        group_sizes[ng]; or mode 2 (the library's choices for a backward of these sizes) and
 //        lines of dtype, ng, ns, tp, ts, h_q, h_kv, d, wide, wide_q, the last two 0 or 1 for a
-//        given tiling or -1 for the library's rule.
+//        given tiling or -1 for the library's rule; or mode 3 / 4 (the final-token call's plan in one
+//        kernel / in two), ng, ns, tp, ts, members per block, most blocks, then the arrays.
 // stdout: error n_qtiles n_kvtiles, then one line per query tile in rank order
 //         ("q kind group row0 row1 aux work chunk nchunks"), the same for kv tiles ("k ..."),
 //         then "s" followed by the per-row member starts (when the plan is valid); in mode 2, per
-//         line: bm bkv kv_chunks split max_q max_kv one_block workspace size_query.
+//         line: bm bkv kv_chunks split max_q max_kv one_block workspace size_query; in modes 3 and 4
+//         error and the number of member blocks, then "b group m_first m_count" per block.
 #include <cstdio>
 #include <memory>
 
@@ -32,13 +34,17 @@ static int print_layouts() {
 }
 
 int main() {
-  int mode, ng, ns, tp, ts, bm, bkv, kvc, split;
-  long max_q, max_kv;
+  int mode, ng, ns, tp, ts, bm = kFwdBM, bkv = kKvBN, kvc = 1, split = 0, mpw = 0, nb_max = 0;
+  long max_q = 0x7fffffffL, max_kv = 0x7fffffffL;
   if (scanf("%d", &mode) != 1) return 2;
   if (mode == 2) return print_layouts();
-  if (scanf("%d %d %d %d %d %d %d %d %ld %ld", &ng, &ns, &tp, &ts, &bm, &bkv, &kvc, &split, &max_q,
-            &max_kv) != 10)
+  const bool last = mode >= 3;
+  if (last) {
+    if (scanf("%d %d %d %d %d %d", &ng, &ns, &tp, &ts, &mpw, &nb_max) != 6) return 2;
+  } else if (scanf("%d %d %d %d %d %d %d %d %ld %ld", &ng, &ns, &tp, &ts, &bm, &bkv, &kvc, &split, &max_q,
+            &max_kv) != 10) {
     return 2;
+  }
   std::unique_ptr<int[]> cu_p(new int[ng + 1]), cu_s(new int[ns + 1]), gsz(new int[ng > 0 ? ng : 1]);
   for (int i = 0; i <= ng; ++i) if (scanf("%d", &cu_p[i]) != 1) return 2;
   for (int i = 0; i <= ns; ++i) if (scanf("%d", &cu_s[i]) != 1) return 2;
@@ -46,6 +52,25 @@ int main() {
   PlanHeader hdr{};
   std::unique_ptr<GroupInfoEx[]> gi(new GroupInfoEx[ng > 0 ? ng : 1]);
   std::unique_ptr<int[]> qoff(new int[ng + 1]), kvoff(new int[ng + 1]);
+  if (last) {
+    std::unique_ptr<LastBlock[]> blocks(new LastBlock[nb_max > 0 ? nb_max : 1]);
+    int n = -1;
+    if (mode == 3) {
+      host_launch(1, kPlanThreads, [&] {
+        plan_last_fused_kernel(cu_p.get(), cu_s.get(), gsz.get(), ng, ns, tp, ts, bm, bkv, &hdr, gi.get(), qoff.get(),
+                               kvoff.get(), mpw, nb_max, blocks.get(), &n);
+      });
+    } else {
+      host_launch(1, kPlanThreads, [&] {
+        plan_groups_kernel(cu_p.get(), cu_s.get(), gsz.get(), ng, ns, tp, ts, bm, bkv, kvc, split, max_q, max_kv, &hdr,
+                           gi.get(), qoff.get(), kvoff.get());
+      });
+      host_launch(1, kPlanThreads, [&] { plan_last_kernel(&hdr, gi.get(), ng, mpw, nb_max, blocks.get(), &n); });
+    }
+    printf("%d %d\n", hdr.error, n);
+    for (int b = 0; b < n; ++b) printf("b %d %d %d\n", blocks[b].group, blocks[b].m_first, blocks[b].m_count);
+    return 0;
+  }
   const long nq_cap = max_q > 0 ? max_q : 1, nkv_cap = max_kv > 0 ? max_kv : 1;
   std::unique_ptr<TileDesc[]> qt(new TileDesc[nq_cap]), kt(new TileDesc[nkv_cap]);
   std::unique_ptr<int[]> qo(new int[nq_cap]), ko(new int[nkv_cap]);

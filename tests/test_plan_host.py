@@ -65,19 +65,31 @@ def run_plan(exe, cu_p, cu_s, gsz, ng, ns, tp, ts, mode=0, kvc=1, split=0, max_q
     bq, bk = bounds(ng, ns, tp, ts, kvc, bm, bkv)
     max_q = bq if max_q is None else max_q
     max_kv = bk if max_kv is None else max_kv
-    text = " ".join(str(int(x)) for x in [mode, ng, ns, tp, ts, bm, bkv, kvc, split, max_q, max_kv, *cu_p, *cu_s,
-                                           *gsz])
-    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0", UBSAN_OPTIONS="halt_on_error=1")
-    res = subprocess.run([exe], input=text, capture_output=True, text=True, env=env, timeout=300)
-    assert res.returncode == 0, res.stderr[-4000:]
-    assert "ERROR: AddressSanitizer" not in res.stderr and "runtime error" not in res.stderr, res.stderr[-4000:]
-    lines = res.stdout.split("\n")
+    lines = _run(exe, [mode, ng, ns, tp, ts, bm, bkv, kvc, split, max_q, max_kv, *cu_p, *cu_s, *gsz])
     err, nq, nkv = (int(x) for x in lines[0].split())
     q = [tuple(int(x) for x in ln.split()[1:]) for ln in lines[1:] if ln.startswith("q ")]
     k = [tuple(int(x) for x in ln.split()[1:]) for ln in lines[1:] if ln.startswith("k ")]
     s = [ln for ln in lines if ln.startswith("s")]
     seg = [int(x) for x in s[0].split()[1:]] if s else []
     return err, q, k, seg
+
+
+def run_last_plan(exe, cu_p, cu_s, gsz, ng, ns, tp, ts, mpw, nb_max, mode):
+    """(error, member blocks) of the final-token call's plan: mode 3 in one kernel, 4 in two."""
+    lines = _run(exe, [mode, ng, ns, tp, ts, mpw, nb_max, *cu_p, *cu_s, *gsz])
+    err, n = (int(x) for x in lines[0].split())
+    blocks = [tuple(int(x) for x in ln.split()[1:]) for ln in lines[1:] if ln.startswith("b ")]
+    assert len(blocks) == n
+    return err, blocks
+
+
+def _run(exe, values):
+    text = " ".join(str(int(x)) for x in values)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0", UBSAN_OPTIONS="halt_on_error=1")
+    res = subprocess.run([exe], input=text, capture_output=True, text=True, env=env, timeout=300)
+    assert res.returncode == 0, res.stderr[-4000:]
+    assert "ERROR: AddressSanitizer" not in res.stderr and "runtime error" not in res.stderr, res.stderr[-4000:]
+    return res.stdout.split("\n")
 
 
 def arrays(prefix, groups, suffix):
@@ -150,15 +162,31 @@ def test_inconsistent_group_sizes_are_flagged_without_out_of_range_reads(planner
     ng = len(gsz)
     cu_p = list(range(ng + 1))          # one prefix row per group: valid
     cu_s = list(range(ns + 1))          # one row per member: valid
+    _all_planners_refuse(planner, cu_p, cu_s, gsz, ng, ns)
+
+
+def _all_planners_refuse(planner, cu_p, cu_s, gsz, tp, ts):
+    """The arrays are flagged: as they are, planned from LDS, and padded with empty groups (in front, so that the
+    fault sits beyond the first pass of 1024) or members to more than LDS holds (plan_groups_kernel from memory, here
+    before plan_last_kernel)."""
+    ng, ns = len(gsz), len(cu_s) - 1
     for mode in (0, 1):
-        err, q, k, _ = run_plan(planner, cu_p, cu_s, gsz, ng, ns, ng, ns, mode=mode)
+        err, q, k, _ = run_plan(planner, cu_p, cu_s, gsz, ng, ns, tp, ts, mode=mode)
         assert err == 1 and not q and not k
+    assert run_last_plan(planner, cu_p, cu_s, gsz, ng, ns, tp, ts, 16, ns + ng, 3) == (1, [])
+    more_groups = ([cu_p[0]] * 1100 + list(cu_p), list(cu_s), [0] * 1100 + list(gsz))
+    more_members = (list(cu_p), list(cu_s) + [cu_s[-1]] * 4097, list(gsz[:-1]) + [gsz[-1] + 4097])
+    if gsz[-1] + 4097 > 0x7FFFFFFF or gsz[-1] < 0:
+        more_members = None
+    for a in filter(None, (more_groups, more_members)):
+        n, m = len(a[2]), len(a[1]) - 1
+        assert run_last_plan(planner, *a, n, m, tp, ts, 16, m + n, 4) == (1, [])
 
 
 @pytest.mark.parametrize("bad", ["cu_p_start", "cu_p_total", "cu_p_order", "cu_s_total", "cu_s_order", "size_sum"])
 def test_inconsistent_offsets_are_flagged(planner, bad):
     cu_p, cu_s, gsz = (list(a) for a in arrays([5, 3], [2, 1], [4, 0, 6]))
-    ng, ns, tp, ts = 2, 3, 8, 10
+    tp, ts = 8, 10
     if bad == "cu_p_start":
         cu_p[0] = 1
     elif bad == "cu_p_total":
@@ -171,9 +199,25 @@ def test_inconsistent_offsets_are_flagged(planner, bad):
         cu_s[1] = 7
     else:
         gsz = [2, 2]
-    for mode in (0, 1):
-        err, q, k, _ = run_plan(planner, cu_p, cu_s, gsz, ng, ns, tp, ts, mode=mode)
-        assert err == 1 and not q and not k
+    _all_planners_refuse(planner, cu_p, cu_s, gsz, tp, ts)
+
+
+@pytest.mark.parametrize("ng,mpw", [(1, 16), (7, 2), (63, 16), (64, 1), (300, 3), (1023, 2), (1024, 2), (2500, 1)])
+def test_member_blocks_of_the_final_token_plan(planner, ng, mpw):
+    """Every group's members in runs of at most mpw, groups in order; both ways of planning where both apply."""
+    rng = np.random.default_rng(ng)
+    groups = rng.integers(0, 5, ng) if ng > 1 else np.array([40])
+    suffix = rng.integers(0, 9, int(groups.sum()))
+    prefix = rng.integers(0, 9, ng)
+    cu_p, cu_s, gsz = arrays(prefix, groups, suffix)
+    ns = len(suffix)
+    want, m = [], 0
+    for g, size in enumerate(groups):
+        want += [(g, m + i, min(mpw, int(size) - i)) for i in range(0, int(size), mpw)]
+        m += int(size)
+    modes = (3, 4) if ng <= 1023 and ns <= 4096 else (4,)
+    for mode in modes:
+        assert run_last_plan(planner, cu_p, cu_s, gsz, ng, ns, cu_p[-1], cu_s[-1], mpw, ns + ng, mode) == (0, want)
 
 
 def expected_tiles(prefix, groups, suffix, kvc, split=0, bm=128, bkv=128):
@@ -278,6 +322,23 @@ def test_random_groupings_plan_as_the_kernels_assume(planner, seed, split, tilin
         work = [t[5] for t in tiles]
         assert work == sorted(work, reverse=True)
     check_loads(prefix, groups, suffix, q, k, seg, 8, 2, 128, "bf16", lay["bm"], lay["bkv"])
+
+
+@pytest.mark.parametrize("pad", ["groups", "members"])
+def test_plan_from_memory_is_the_plan_from_lds(planner, pad):
+    """Empty groups or members behind the others, more than LDS holds, change no tile."""
+    rng = np.random.default_rng(21)
+    prefix, groups = rng.integers(0, 500, 40), rng.integers(0, 5, 40)
+    suffix = rng.integers(0, 300, int(groups.sum()))
+    cu_p, cu_s, gsz = (list(a) for a in arrays(prefix, groups, suffix))
+    plans = []
+    for extra in (0, 1100 if pad == "groups" else 4097):
+        if pad == "groups":
+            a = (cu_p + cu_p[-1:] * extra, cu_s, gsz + [0] * extra)
+        else:
+            a = (cu_p, cu_s + cu_s[-1:] * extra, gsz[:-1] + [gsz[-1] + extra])
+        plans.append(run_plan(planner, *a, len(a[2]), len(a[1]) - 1, cu_p[-1], cu_s[-1], mode=1))
+    assert plans[0] == plans[1] and plans[0][0] == 0
 
 
 @pytest.mark.parametrize("ng", [1, 62, 63, 64, 65, 128, 500])
