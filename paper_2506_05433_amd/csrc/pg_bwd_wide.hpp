@@ -436,7 +436,8 @@ __global__ void __launch_bounds__(kWideThreads, 1) dq_wide_kernel(const BwdArgs 
   constexpr int BN = kWideBK;
   constexpr int KK = D / 16, DB = D / 32;
   constexpr int NBUF = 4;
-  constexpr int PF = D == 128 ? 3 : 2;  // row fragments read ahead of their products
+  static_assert(D == 128, "the library runs head_dim 64 on dq_kernel (use_wide_q)");
+  constexpr int PF = 3;                 // row fragments read ahead of their products
   constexpr int AHEAD = 3;              // transposed fragments read ahead
   // AGPRs: dQ^T blocks (qb, db) from a0, then the B operands Q and dO
   constexpr int RQ = 32 * DB, RG = RQ + 8 * KK;
