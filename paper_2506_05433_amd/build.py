@@ -30,7 +30,8 @@ def command(out: str = OUT, extra=()) -> list:
             # results of matrix products that vector instructions read next stay in VGPRs also in
             # kernels that use AGPRs (pg_bwd_wide.hpp keeps its accumulators there). Of the other
             # kernels it changes the fp32 head_dim 128 forward, dQ and final-token ones (864, 343 and
-            # 576 copies between VGPRs and AGPRs become 53, 28 and 32); the code of the bf16 ones is the same
+            # 576 copies between VGPRs and AGPRs become 53, 28 and 32; an fp32 step of 2 x 4, P 257..900,
+            # 8/4 heads 601 -> 591 us); the code of the bf16 ones is the same
             "-mllvm", "-amdgpu-mfma-vgpr-form=1",
             "-o", out, SRC, *extra]
 

@@ -15,8 +15,9 @@
 // sit in AGPRs named in the instructions.
 //
 // Measured on 8 groups x 16 members, P 1246..26888, 64/8 heads, d 128: 240.1 -> 203.2 ms (1190 TFLOP/s of
-// its four products; matrix cores 63% busy at 1.81 GHz); 1 x 16, P 16384, 32/8: 7.35 -> 6.17 ms with the
-// reduction; 1 x 8, P 4096, 32/8: 1.056 -> 0.909 ms; 4 x 16, P 8192, 32/8, d 64: 16.05 -> 13.89 ms.
+// its four products; matrix cores 63% busy at 1.81 GHz); 1 x 16, P 16384, 32/8: 7.35 -> 6.30 ms; 1 x 8, P 4096, 32/8:
+// 1.056 -> 0.909 ms with the reduction; 4 x 16, P 8192, 32/8, d 64: 16.05 -> 13.89 ms. Waves there (one per SIMD) issue
+// 55% of their time, wait for a dependency 24% and to issue 21% (dq_wide_kernel 57, 21 and 23%).
 // Measured and not kept: V (or more of K) in LDS instead of registers; S, dP, dV, dK each in turn with
 // P beside dP and dS beside dV only (3% slower: the vector work does not fit those phases); two wait
 // states before every product instead of before the first that reads new operands (2% slower).
