@@ -98,9 +98,10 @@ inline bool use_wide(int dtype, int ng, int tp, int ts, int h_q, int h_kv) {
 // Whether the backward runs dq_wide_kernel (256-row query tiles). Its workgroups have a CU to themselves,
 // so loading their rows and storing dQ is not hidden: it needs long key walks, and enough tiles to give
 // every CU two. Measured (dq_kernel -> wide), one group of 16/4 or 32/8 heads: P 1024 1278 -> 1468 us, 4096
-// 2477 -> 2500 us, 8192 804 -> 770 us, 16384 4664 -> 4420 us; over random shapes of 128-wide heads, 0.96 of
-// dq_kernel's time on this side of the lines (0.94..1.02), 1.03 below 8192 rows, 1.09 below 4096, 1.2 below 2000. With 64-wide heads the vector work per
-// product doubles and one wave per SIMD cannot issue it (206 -> 278 us on prefixes of 179..2530).
+// 2477 -> 2500 us, 8192 804 -> 770 us, 16384 4664 -> 4420 us; over 166 random shapes of 128-wide heads, 0.96 of
+// dq_kernel's time on this side of the lines (0.94..1.02), 1.03 below 8192 rows, 1.09 below 4096, 1.2 below
+// 2000. With 64-wide heads the vector work per product doubles and one wave per SIMD cannot issue it
+// (206 -> 278 us on prefixes of 179..2530).
 inline bool use_wide_q(int dtype, int ng, int tp, int ts, int h_q, int d) {
   return dtype == PG_BF16 && d == 128 && ng > 0 && tp / 8192 >= ng &&
          (ceil_div_l(tp, kWideBM) + ceil_div_l(ts, kWideBM)) * h_q >= 512;
